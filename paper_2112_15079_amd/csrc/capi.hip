@@ -57,7 +57,11 @@ constexpr int64_t kMaxBodies = (int64_t)1 << 30;
 // tile table
 
 std::mutex g_mu;
-std::map<std::tuple<int, int, int>, Tile> g_tiles;   // (kind, precision, size class)
+struct TunedTile {
+    Tile tile;
+    bool forced;   // nbody_set_tile (runs then take this tile at any size)
+};
+std::map<std::tuple<int, int, int>, TunedTile> g_tiles;   // (kind, precision, size class)
 
 constexpr int kBatchChunkMax = 16;
 // Partial slots of an ensemble's workspace: the one-way passes use at most
@@ -174,16 +178,109 @@ Tile pick_tile(int kind, int prec, int64_t n)
     {
         std::lock_guard<std::mutex> lk(g_mu);
         auto it = g_tiles.find(std::make_tuple(kind, prec, size_class(n)));
-        if (it != g_tiles.end() && !(it->second.variant == 3 && n > kSmallMax) &&
-            !(it->second.variant == 5 && !mutual_fits(kind, prec, n)) &&
-            !(prec == NBODY_SPLIT_COMPENSATED && it->second.variant != 5)) {
-            Tile t = it->second;
+        if (it != g_tiles.end() && !(it->second.tile.variant == 3 && n > kSmallMax) &&
+            !(it->second.tile.variant == 5 && !mutual_fits(kind, prec, n)) &&
+            !(prec == NBODY_SPLIT_COMPENSATED && it->second.tile.variant != 5)) {
+            Tile t = it->second.tile;
             t.chunks = std::min(t.chunks, chunk_cap(n));
             return t;
         }
     }
     return heuristic_tile(kind, prec, n);
 }
+
+// ---------------------------------------------------------------------------
+// the workgroups that stay on the chip (kernels_group.hip)
+
+// Runs of single systems of these sizes take the group kernel unless
+// nbody_set_tile chose a tile for the size (us per step, FP64, 300-step runs:
+// 1.55 against 1.43 with one workgroup alone at 64 bodies, 1.76 against 2.44 at
+// 100; 16.0 against 20.8 each pair once at 4,095: above, 256 workgroups of 16
+// targets would not hold the system, nor LDS its sources).
+constexpr int64_t kGroupMin = 80;
+constexpr int64_t kGroupMax = 4095;
+
+// The group kernel's shape for n bodies: few enough targets per workgroup that
+// the chip's 256 CUs are used, one workgroup each (us per step at 1,000
+// bodies: 3.4 with 250 workgroups of 4 targets, 4.0 with 125 of 8), with two
+// waves per SIMD where a round's latency hides behind them (1,000 bodies: 3.4
+// with 1,024 threads, 3.7 with 512; 500 bodies: 2.6 and 2.5).
+GroupShape group_shape(int64_t n)
+{
+    if (n <= 256) return {1, 8, 512};
+    if (n <= 768) return {1, 4, 512};
+    if (n <= 1024) return {1, 4, 1024};
+    if (n <= 2048) return {2, 4, 512};
+    if (n <= 3072) return {3, 4, 1024};
+    return {4, 4, 512};
+}
+
+// Up to 256 bodies the at most 32 workgroups are placed on one XCD (one in eight
+// of those launched: workgroups go to the XCDs in turn), whose L2 then carries
+// the exchange: 1.8 against 2.1 us per step at 131 bodies.
+int group_spread(int64_t n) { return n <= 256 ? 8 : 1; }
+
+// Whether a run (or force evaluation) of a single system takes it.
+bool group_route(int prec, int64_t n)
+{
+    if (prec == NBODY_SPLIT_COMPENSATED || n < kGroupMin || n > kGroupMax) return false;
+    std::lock_guard<std::mutex> lk(g_mu);
+    auto it = g_tiles.find(std::make_tuple(0, prec, size_class(n)));
+    return it == g_tiles.end() || !it->second.forced;
+}
+
+// Launch indices of one launch: as many steps as a run whose registration
+// found part of the workgroups missing goes on with the others' share.
+constexpr int64_t kGroupSegment = 1024;
+
+// Launch indices 0 .. last of a run of `steps` steps by the group kernel,
+// state in pos, vel (with traj the positions after each drift are stored and
+// pos is only read); or, with acc, the accelerations at pos.  xbuf: 12 n
+// doubles, 16-byte aligned; reg: two words (both unused when last = 0).
+int group_launches(int prec, const double* pos_in, double* pos_out, double* vel,
+                   const double* mass, int64_t n, const int64_t* nmaj, double G, double dt,
+                   int64_t last, int64_t steps, double* acc, double* traj, double* xbuf,
+                   uint32_t* reg, uint32_t* flags, hipStream_t s)
+{
+    const double* rin = pos_in;
+    for (int64_t a = 0; a <= last;) {
+        // (never one index alone that drifts: it would write where others read)
+        int64_t b = std::min(a + kGroupSegment - 1, last);
+        if (last - b == 1) b = last;
+        GroupArgs A{};
+        A.pos_in = rin;
+        A.pos_out = pos_out;
+        A.vel = vel;
+        A.mass = mass;
+        A.xbuf = xbuf;
+        A.reg = reg;
+        A.nmaj = nmaj;
+        A.acc = acc;
+        A.traj = traj ? traj + a * 3 * n : nullptr;
+        A.flags = flags;
+        A.n = n;
+        A.stride = n;
+        A.G = G;
+        A.dt = dt;
+        A.i0 = a;
+        A.i1 = b;
+        A.steps = steps;
+        A.spread = group_spread(n);
+        const GroupShape g = group_shape(n);
+        const int64_t tw = (int64_t)g.tpl * g.lanes;
+        NB_HIP(launch_group(prec == NBODY_SPLIT ? 1 : 0, g, A, (int)((n + tw - 1) / tw), n, 12 * n,
+                            1, s));
+        // a launch that stores nothing but the trajectory hands its last
+        // position on through the trajectory buffer
+        rin = pos_out ? pos_out : A.traj ? A.traj + (b - a) * 3 * n : nullptr;
+        a = b + 1;
+    }
+    return NBODY_OK;
+}
+
+// The registration words of a workspace: behind the flags word (two for the
+// caller's stream, two for the adjoint's second).
+uint32_t* group_reg(uint32_t* flags) { return flags + 16; }
 
 // ---------------------------------------------------------------------------
 // workspace layout
@@ -663,9 +760,13 @@ int32_t nbody_accel(const double* pos, const double* vel, const double* mass, in
     double* part = at<double>(workspace, L.part);
     uint32_t* flags = at<uint32_t>(workspace, L.flags);
     double* gm = at<double>(workspace, L.gm);
+    const bool group = group_route(precision, n);
     const bool small = tile.variant == 3;
     const bool fused = tile.variant == 4;
     if (precision == NBODY_FP64) {
+        if (group)
+            return group_launches(0, pos, nullptr, nullptr, mass, n, nullptr, G, 0.0, 0, 0,
+                                  acc_out, nullptr, nullptr, nullptr, flags, s);
         if (small) {
             NB_HIP(launch_run_small(0, tile, pos, nullptr, nullptr, mass, n, nullptr, G, 0.0, 0, 0,
                                     0, acc_out, nullptr, flags, s));
@@ -689,7 +790,11 @@ int32_t nbody_accel(const double* pos, const double* vel, const double* mass, in
     double* acc_c = at<double>(workspace, L.alt_c);
     NB_HIP(launch_gather(perm, n, pos, pos_c, 3, s));
     NB_HIP(launch_gather(perm, n, mass, mass_c, 1, s));
-    if (small) {
+    if (group) {
+        NB_TRY(group_launches(precision, pos_c, nullptr, nullptr, mass_c, n,
+                              at<int64_t>(workspace, L.nmaj), G, 0.0, 0, 0, acc_c, nullptr,
+                              nullptr, nullptr, flags, s));
+    } else if (small) {
         NB_HIP(launch_run_small(1, tile, pos_c, nullptr, nullptr, mass_c, n,
                                 at<int64_t>(workspace, L.nmaj), G, 0.0, 0, 0, 0, acc_c, nullptr,
                                 flags, s));
@@ -744,8 +849,12 @@ int verlet_run_on(double* pos, double* vel, const double* mass, int64_t n, doubl
     double* alt = at<double>(ws, L.alt);
     double* gm = at<double>(ws, L.gm);
     P.gm = gm;
+    const bool group = group_route(precision, n);
     const bool small = P.tile.variant == 3;
     if (precision == NBODY_FP64) {
+        if (group)
+            return group_launches(0, pos, pos, vel, mass, n, nullptr, G, dt, steps, steps,
+                                  nullptr, nullptr, P.part, group_reg(P.flags), P.flags, s);
         if (small) {
             NB_HIP(launch_run_small(0, P.tile, pos, pos, vel, mass, n, nullptr, G, dt, 0, steps,
                                     steps, nullptr, nullptr, P.flags, s));
@@ -774,9 +883,14 @@ int verlet_run_on(double* pos, double* vel, const double* mass, int64_t n, doubl
     NB_HIP(launch_gather(perm, n, vel, vel_c, 3, s));
     NB_HIP(launch_gather(perm, n, mass, mass_c, 1, s));
     P.nmaj = at<int64_t>(ws, L.nmaj);
-    if (small) {
-        NB_HIP(launch_run_small(1, P.tile, pos_c, pos_c, vel_c, mass_c, n, P.nmaj, G, dt, 0, steps,
-                                steps, nullptr, nullptr, P.flags, s));
+    if (group || small) {
+        if (group)
+            NB_TRY(group_launches(precision, pos_c, pos_c, vel_c, mass_c, n, P.nmaj, G, dt,
+                                  steps, steps, nullptr, nullptr, P.part, group_reg(P.flags),
+                                  P.flags, s));
+        else
+            NB_HIP(launch_run_small(1, P.tile, pos_c, pos_c, vel_c, mass_c, n, P.nmaj, G, dt, 0,
+                                    steps, steps, nullptr, nullptr, P.flags, s));
         NB_HIP(launch_scatter(perm, n, pos_c, pos, 3, s));
         NB_HIP(launch_scatter(perm, n, vel_c, vel, 3, s));
         return NBODY_OK;
@@ -986,7 +1100,7 @@ int32_t nbody_set_tile(int32_t kind, int32_t precision, int64_t n, const nbody_t
         return fail(NBODY_EINVAL, "unsupported tile (%d, %d, %d, variant %d) for kind %d",
                     t.tpl, t.waves, t.chunks, t.variant, kind);
     std::lock_guard<std::mutex> lk(g_mu);
-    g_tiles[std::make_tuple(kind, precision, size_class(n))] = t;
+    g_tiles[std::make_tuple(kind, precision, size_class(n))] = TunedTile{t, true};
     return NBODY_OK;
 }
 
@@ -1052,6 +1166,7 @@ static int adjoint_core(const double* pos0, const double* vel0, const double* ma
     P.vel = wv;
     P.buf[0] = w0;
     P.buf[1] = w1;
+    const bool group = group_route(NBODY_FP64, n);
     const bool small = P.tile.variant == 3;
     const Tile vt = pick_tile(1, NBODY_FP64, n);
     const int vchunks = vjp_chunks(n, vt);
@@ -1085,7 +1200,10 @@ static int adjoint_core(const double* pos0, const double* vel0, const double* ma
             NB_HIP(hipMemcpyAsync(w0, ck_r(c), b3, hipMemcpyDeviceToDevice, s));
             NB_HIP(hipMemcpyAsync(wv, ck_v(c), b3, hipMemcpyDeviceToDevice, s));
             const double* r_end = w0;
-            if (small) {
+            if (group) {
+                NB_TRY(group_launches(0, w0, w0, wv, mass, n, nullptr, G, dt, kseg, kseg, nullptr,
+                                      nullptr, part, group_reg(flags), flags, s));
+            } else if (small) {
                 NB_HIP(launch_run_small(0, P.tile, w0, w0, wv, mass, n, nullptr, G, dt, 0, kseg, kseg,
                                         nullptr, nullptr, flags, s));
             } else {
@@ -1136,7 +1254,13 @@ static int adjoint_core(const double* pos0, const double* vel0, const double* ma
         if (freed_recorded[b]) NB_HIP(hipStreamWaitEvent(sb, side->freed[b], 0));
         NB_HIP(hipMemcpyAsync(sg, ck_r(c), b3, hipMemcpyDeviceToDevice, sb));
         NB_HIP(hipMemcpyAsync(vtmp2, ck_v(c), b3, hipMemcpyDeviceToDevice, sb));
-        NB_TRY(maybe_graph_on(sb, key_of(3, kseg, 0, sg), kseg, [&](hipStream_t cs) -> int {
+        if (group) {
+            // (the segment's positions r_{cK+1} .. r_{cK+kseg-1}, as below)
+            if (kseg >= 2)
+                NB_TRY(group_launches(0, sg, nullptr, vtmp2, mass, n, nullptr, G, dt, kseg - 2,
+                                      kseg, nullptr, sg + 3 * n, part2, group_reg(flags) + 2,
+                                      flags, sb));
+        } else NB_TRY(maybe_graph_on(sb, key_of(3, kseg, 0, sg), kseg, [&](hipStream_t cs) -> int {
             // positions r_{cK+1} .. r_{cK+kseg-1} of the segment into its slots
             if (small && kseg >= 2)
                 NB_HIP(launch_run_small(0, R.tile, sg, nullptr, vtmp2, mass, n, nullptr, G, dt, 0,
@@ -1402,7 +1526,7 @@ Tile batch_tile(int prec, const int64_t* offs, int32_t ns)
     {
         std::lock_guard<std::mutex> lk(g_mu);
         auto it = g_tiles.find(std::make_tuple(2, prec, size_class(0)));
-        if (it != g_tiles.end()) return it->second;
+        if (it != g_tiles.end()) return it->second.tile;
     }
     double sn = 0.0, sn2 = 0.0;
     bool fits = true;
@@ -1703,7 +1827,7 @@ int32_t nbody_autotune_batched(int32_t precision, const double* pos, const doubl
     if (status != NBODY_OK) return status;
     {
         std::lock_guard<std::mutex> lk(g_mu);
-        g_tiles[std::make_tuple(2, (int)precision, size_class(0))] = best;
+        g_tiles[std::make_tuple(2, (int)precision, size_class(0))] = TunedTile{best, false};
     }
     if (best_host) {
         best_host->targets_per_lane = best.tpl;
@@ -1932,7 +2056,7 @@ int32_t nbody_autotune(int32_t kind, int32_t precision, const double* pos, const
     if (status != NBODY_OK) return status;
     {
         std::lock_guard<std::mutex> lk(g_mu);
-        g_tiles[std::make_tuple(kind, precision, size_class(n))] = best;
+        g_tiles[std::make_tuple(kind, precision, size_class(n))] = TunedTile{best, false};
     }
     if (best_host) {
         best_host->targets_per_lane = best.tpl;

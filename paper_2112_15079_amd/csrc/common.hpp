@@ -122,6 +122,45 @@ hipError_t launch_run_small(int precision, const Tile& tile, const double* pos_i
                             int64_t steps, double* acc, double* traj, uint32_t* flags,
                             hipStream_t s);
 
+// ----- whole runs by several workgroups that stay on the chip -----------------
+// Shape of one launch: `tpl` targets per lane, `lanes` lanes side by side on
+// different targets, `threads` per workgroup; a workgroup's virtual groups
+// hold tpl * lanes targets each.
+struct GroupShape {
+    int tpl, lanes, threads;
+};
+// An ensemble's workgroup: its system and how many workgroups that has.
+struct GroupUnit {
+    int64_t body0;
+    int32_t n;
+    int32_t sys;
+    int32_t workgroups;
+    int32_t rank;       // among the system's workgroups (one-index launches)
+};
+struct GroupArgs {
+    const double* pos_in;
+    double* pos_out;        // may be pos_in when i1 > i0; NULL: not stored
+    double* vel;
+    const double* mass;
+    double* xbuf;           // 12 words per body (i1 > i0), 16-byte aligned
+    uint32_t* reg;          // 2 words per system (i1 > i0)
+    const GroupUnit* units; // NULL: one system of n bodies
+    const int64_t* nmaj;    // split form
+    double* acc;            // NULL or a(r)
+    double* traj;           // NULL or the positions after each drift, 3 n a launch index
+    uint32_t* flags;
+    int64_t n, stride;      // bodies of the system (of all systems), plane stride
+    double G, dt;
+    int64_t i0, i1, steps;  // launch indices as in launch_run_small
+    int spread;             // one workgroup of every `spread` launched takes part
+};
+#define NB_GROUP_SHAPES(X)                                                            \
+    X(1, 8, 512) X(1, 4, 512) X(1, 4, 1024) X(2, 4, 512) X(3, 4, 1024) X(4, 4, 512)
+size_t group_lds_bytes(int64_t n, const GroupShape& g);
+// n_max: bodies of the largest system; words: exchange words to reset.
+hipError_t launch_group(int precision, const GroupShape& g, const GroupArgs& A, int blocks,
+                        int64_t n_max, int64_t words, int nsys, hipStream_t s);
+
 // ----- step epilogue (Eqs. (3)-(4) as kick-drift-kick) -----------------------
 enum StepMode : int {
     kStoreAcc = 1,   // write a to acc
