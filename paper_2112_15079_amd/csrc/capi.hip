@@ -233,49 +233,57 @@ bool group_route(int prec, int64_t n)
 // found part of the workgroups missing goes on with the others' share.
 constexpr int64_t kGroupSegment = 1024;
 
-// Launch indices 0 .. last of a run of `steps` steps by the group kernel,
-// state in pos, vel (with traj the positions after each drift are stored and
-// pos is only read); or, with acc, the accelerations at pos.  xbuf: 12 n
-// doubles, 16-byte aligned; reg: two words (both unused when last = 0).
-int group_launches(int prec, const double* pos_in, double* pos_out, double* vel,
-                   const double* mass, int64_t n, const int64_t* nmaj, double G, double dt,
-                   int64_t last, int64_t steps, double* acc, double* traj, double* xbuf,
-                   uint32_t* reg, uint32_t* flags, hipStream_t s)
+// Launch indices 0 .. last of a run by the group kernel: A with everything but
+// the indices, in `blocks` workgroups; n_max: the largest of nsys systems.
+int group_launches(int prec, const GroupShape& g, GroupArgs A, int blocks, int64_t n_max, int nsys,
+                   int64_t last, hipStream_t s)
 {
-    const double* rin = pos_in;
+    double* const traj = A.traj;
     for (int64_t a = 0; a <= last;) {
         // (never one index alone that drifts: it would write where others read)
         int64_t b = std::min(a + kGroupSegment - 1, last);
         if (last - b == 1) b = last;
-        GroupArgs A{};
-        A.pos_in = rin;
-        A.pos_out = pos_out;
-        A.vel = vel;
-        A.mass = mass;
-        A.xbuf = xbuf;
-        A.reg = reg;
-        A.nmaj = nmaj;
-        A.acc = acc;
-        A.traj = traj ? traj + a * 3 * n : nullptr;
-        A.flags = flags;
-        A.n = n;
-        A.stride = n;
-        A.G = G;
-        A.dt = dt;
+        A.traj = traj ? traj + a * 3 * A.n : nullptr;
         A.i0 = a;
         A.i1 = b;
-        A.steps = steps;
-        A.spread = group_spread(n);
-        const GroupShape g = group_shape(n);
-        const int64_t tw = (int64_t)g.tpl * g.lanes;
-        NB_HIP(launch_group(prec == NBODY_SPLIT ? 1 : 0, g, A, (int)((n + tw - 1) / tw), n, 12 * n,
-                            1, s));
+        NB_HIP(launch_group(prec == NBODY_SPLIT ? 1 : 0, g, A, blocks, n_max, 12 * A.n, nsys, s));
         // a launch that stores nothing but the trajectory hands its last
         // position on through the trajectory buffer
-        rin = pos_out ? pos_out : A.traj ? A.traj + (b - a) * 3 * n : nullptr;
+        A.pos_in = A.pos_out ? A.pos_out : A.traj ? A.traj + (b - a) * 3 * A.n : nullptr;
         a = b + 1;
     }
     return NBODY_OK;
+}
+
+// ... of a single system of n bodies, a run of `steps` steps with the state in
+// pos, vel (with traj the positions after each drift are stored and pos is only
+// read); or, with acc, the accelerations at pos.  xbuf: 12 n doubles, 16-byte
+// aligned; reg: two words (both unused when last = 0).
+int group_run(int prec, const double* pos_in, double* pos_out, double* vel, const double* mass,
+              int64_t n, const int64_t* nmaj, double G, double dt, int64_t last, int64_t steps,
+              double* acc, double* traj, double* xbuf, uint32_t* reg, uint32_t* flags,
+              hipStream_t s)
+{
+    GroupArgs A{};
+    A.pos_in = pos_in;
+    A.pos_out = pos_out;
+    A.vel = vel;
+    A.mass = mass;
+    A.xbuf = xbuf;
+    A.reg = reg;
+    A.nmaj = nmaj;
+    A.acc = acc;
+    A.traj = traj;
+    A.flags = flags;
+    A.n = n;
+    A.stride = n;
+    A.G = G;
+    A.dt = dt;
+    A.steps = steps;
+    A.spread = group_spread(n);
+    const GroupShape g = group_shape(n);
+    const int64_t tw = (int64_t)g.tpl * g.lanes;
+    return group_launches(prec, g, A, (int)((n + tw - 1) / tw), n, 1, last, s);
 }
 
 // The registration words of a workspace: behind the flags word (two for the
@@ -765,7 +773,7 @@ int32_t nbody_accel(const double* pos, const double* vel, const double* mass, in
     const bool fused = tile.variant == 4;
     if (precision == NBODY_FP64) {
         if (group)
-            return group_launches(0, pos, nullptr, nullptr, mass, n, nullptr, G, 0.0, 0, 0,
+            return group_run(0, pos, nullptr, nullptr, mass, n, nullptr, G, 0.0, 0, 0,
                                   acc_out, nullptr, nullptr, nullptr, flags, s);
         if (small) {
             NB_HIP(launch_run_small(0, tile, pos, nullptr, nullptr, mass, n, nullptr, G, 0.0, 0, 0,
@@ -791,7 +799,7 @@ int32_t nbody_accel(const double* pos, const double* vel, const double* mass, in
     NB_HIP(launch_gather(perm, n, pos, pos_c, 3, s));
     NB_HIP(launch_gather(perm, n, mass, mass_c, 1, s));
     if (group) {
-        NB_TRY(group_launches(precision, pos_c, nullptr, nullptr, mass_c, n,
+        NB_TRY(group_run(precision, pos_c, nullptr, nullptr, mass_c, n,
                               at<int64_t>(workspace, L.nmaj), G, 0.0, 0, 0, acc_c, nullptr,
                               nullptr, nullptr, flags, s));
     } else if (small) {
@@ -853,7 +861,7 @@ int verlet_run_on(double* pos, double* vel, const double* mass, int64_t n, doubl
     const bool small = P.tile.variant == 3;
     if (precision == NBODY_FP64) {
         if (group)
-            return group_launches(0, pos, pos, vel, mass, n, nullptr, G, dt, steps, steps,
+            return group_run(0, pos, pos, vel, mass, n, nullptr, G, dt, steps, steps,
                                   nullptr, nullptr, P.part, group_reg(P.flags), P.flags, s);
         if (small) {
             NB_HIP(launch_run_small(0, P.tile, pos, pos, vel, mass, n, nullptr, G, dt, 0, steps,
@@ -885,7 +893,7 @@ int verlet_run_on(double* pos, double* vel, const double* mass, int64_t n, doubl
     P.nmaj = at<int64_t>(ws, L.nmaj);
     if (group || small) {
         if (group)
-            NB_TRY(group_launches(precision, pos_c, pos_c, vel_c, mass_c, n, P.nmaj, G, dt,
+            NB_TRY(group_run(precision, pos_c, pos_c, vel_c, mass_c, n, P.nmaj, G, dt,
                                   steps, steps, nullptr, nullptr, P.part, group_reg(P.flags),
                                   P.flags, s));
         else
@@ -1201,7 +1209,7 @@ static int adjoint_core(const double* pos0, const double* vel0, const double* ma
             NB_HIP(hipMemcpyAsync(wv, ck_v(c), b3, hipMemcpyDeviceToDevice, s));
             const double* r_end = w0;
             if (group) {
-                NB_TRY(group_launches(0, w0, w0, wv, mass, n, nullptr, G, dt, kseg, kseg, nullptr,
+                NB_TRY(group_run(0, w0, w0, wv, mass, n, nullptr, G, dt, kseg, kseg, nullptr,
                                       nullptr, part, group_reg(flags), flags, s));
             } else if (small) {
                 NB_HIP(launch_run_small(0, P.tile, w0, w0, wv, mass, n, nullptr, G, dt, 0, kseg, kseg,
@@ -1257,7 +1265,7 @@ static int adjoint_core(const double* pos0, const double* vel0, const double* ma
         if (group) {
             // (the segment's positions r_{cK+1} .. r_{cK+kseg-1}, as below)
             if (kseg >= 2)
-                NB_TRY(group_launches(0, sg, nullptr, vtmp2, mass, n, nullptr, G, dt, kseg - 2,
+                NB_TRY(group_run(0, sg, nullptr, vtmp2, mass, n, nullptr, G, dt, kseg - 2,
                                       kseg, nullptr, sg + 3 * n, part2, group_reg(flags) + 2,
                                       flags, sb));
         } else NB_TRY(maybe_graph_on(sb, key_of(3, kseg, 0, sg), kseg, [&](hipStream_t cs) -> int {
@@ -1387,6 +1395,8 @@ struct BatchPlan {
     std::vector<BatchUnit> units;
     std::vector<int8_t> bchunks;
     std::vector<int64_t> offsets;
+    std::vector<GroupUnit> group_units;   // the group kernel's list instead
+    int64_t n_max = 0;
 };
 
 // Work lists of recent ensembles (host memory; uploaded each run).  At most
@@ -1607,6 +1617,121 @@ int batched_split_prepare(const double* pos, const double* vel, const double* ma
     return NBODY_OK;
 }
 
+// Whether an ensemble runs in the group kernel (and in which shape, with how
+// many workgroups at once): systems of up to kGroupBatchMax bodies too small
+// on average for each pair once, and not so many that the chip is full anyway,
+// where the one-way passes' leaner pair loop wins (us per step against them:
+// 128 systems of 40 to 400 bodies 9.3 / 53, 8 of 300 to 2,000 28 / 109, 120 of
+// 300 to 1,400, 1.1e8 pairs, 102 / 162: 1.07e12 pairs/s against their 1.49e12
+// when the chip is full, and a tail of 50 to 100 us).
+constexpr int64_t kGroupBatchMax = 2048;
+constexpr double kGroupBatchPairs = 3e8;
+
+bool batch_group_route(int prec, const int64_t* offs, int32_t ns, GroupShape* shape, int* slots)
+{
+    if (prec == NBODY_SPLIT_COMPENSATED) return false;
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        auto it = g_tiles.find(std::make_tuple(2, prec, size_class(0)));
+        if (it != g_tiles.end() && it->second.forced) return false;
+    }
+    int64_t n_max = 0;
+    double pairs = 0.0;
+    for (int32_t k = 0; k < ns; ++k) {
+        const int64_t nk = offs[k + 1] - offs[k];
+        n_max = std::max(n_max, nk);
+        pairs += (double)nk * (double)nk;
+    }
+    const int64_t n = offs[ns];
+    if (n_max > kGroupBatchMax || pairs > kGroupBatchPairs ||
+        pairs >= (double)kBatchMutualMin * (double)n)
+        return false;
+    // targets per workgroup: as many as leave every CU a few workgroups; four
+    // waves each, so that one workgroup's exchange hides behind the others' pairs
+    int per_cu = 2;
+    if (n <= 1024) *shape = {1, 4, 512};
+    else if (n <= 4096) *shape = {2, 4, 512};
+    else if (n <= 12288) *shape = {2, 8, 256}, per_cu = 4;
+    else if (n_max <= 640) *shape = {2, 16, 256}, per_cu = 4;
+    else *shape = {4, 8, 256};
+    const size_t lds = group_lds_bytes(n_max, *shape) + 512;
+    per_cu = (int)std::min<size_t>(per_cu, ((size_t)160 << 10) / lds);
+    *slots = 256 * std::max(per_cu, 1);
+    return true;
+}
+
+// The group kernel's work list: the workgroups that fit on the chip at once
+// (`slots`) are dealt to the systems so that the longest share is as short as
+// it can be; a system's workgroups go to one XCD (workgroups go to the XCDs in
+// turn), whose L2 then carries its exchange.
+std::shared_ptr<BatchPlan> batch_group_plan(const int64_t* offs, int32_t ns, const GroupShape& g,
+                                            int slots)
+{
+    std::vector<int64_t> key(offs, offs + ns + 1);
+    for (int64_t x : {-2, g.tpl, g.lanes, g.threads, slots}) key.push_back(x);
+    std::lock_guard<std::mutex> lk(g_mu);
+    g_batch_used[key] = ++g_batch_tick;
+    auto it = g_batch.find(key);
+    if (it != g_batch.end()) return it->second;
+    evict_batch_plan_locked();
+    auto bp = std::make_shared<BatchPlan>();
+    const int64_t tw = (int64_t)g.tpl * g.lanes;
+    std::vector<int32_t> wgs(ns), order(ns);
+    auto size = [&](int32_t k) { return offs[k + 1] - offs[k]; };
+    // a workgroup that takes r virtual groups of a system of n bodies needs about
+    // r (n + 64): the workgroups needed when no share takes longer than `time`
+    auto needed = [&](double time) {
+        int64_t sum = 0;
+        for (int32_t k = 0; k < ns; ++k) {
+            const int64_t groups = (size(k) + tw - 1) / tw;
+            const double r = std::floor(time / (double)(size(k) + 64));
+            const int64_t share = std::max<int64_t>(1, r < (double)groups ? (int64_t)r : groups);
+            wgs[k] = (int32_t)((groups + share - 1) / share);
+            sum += wgs[k];
+        }
+        return sum;
+    };
+    double lo = 0.0, hi = 0.0;   // hi: every system has one workgroup
+    for (int32_t k = 0; k < ns; ++k) {
+        bp->n_max = std::max(bp->n_max, size(k));
+        hi = std::max(hi, (double)(size(k) + 64) * (double)((size(k) + tw - 1) / tw));
+        order[k] = k;
+    }
+    for (int step = 0; step < 60 && hi - lo > 1.0; ++step) {
+        const double mid = 0.5 * (lo + hi);
+        (needed(mid) <= slots ? hi : lo) = mid;
+    }
+    (void)needed(hi);
+    std::stable_sort(order.begin(), order.end(),
+                     [&](int32_t a, int32_t b) { return size(a) > size(b); });
+    // one list per XCD; a system that no list has room for is spread over all
+    constexpr int kXcds = 8;
+    std::vector<GroupUnit> lists[kXcds];
+    auto shortest = [&] {
+        return std::min_element(lists, lists + kXcds, [](const auto& a, const auto& b) {
+            return a.size() < b.size();
+        });
+    };
+    for (int32_t k : order) {
+        auto* l = shortest();
+        const bool whole = (int64_t)l->size() + wgs[k] <= slots / kXcds;
+        for (int32_t r = 0; r < wgs[k]; ++r)
+            (whole ? l : shortest())->push_back(
+                GroupUnit{offs[k], (int32_t)size(k), k, wgs[k], r});
+    }
+    // in turn, short lists padded (n = 0); unpadded, and so without regard to
+    // XCDs, where the padding would outgrow the workspace's room for units
+    size_t len = 0;
+    for (const auto& l : lists) len = std::max(len, l.size());
+    const bool pad = (int64_t)(kXcds * len) <= offs[ns] / 4 + ns;
+    for (size_t i = 0; i < len; ++i)
+        for (const auto& l : lists)
+            if (i < l.size()) bp->group_units.push_back(l[i]);
+            else if (pad) bp->group_units.push_back(GroupUnit{0, 0, 0, 1, 0});
+    g_batch[key] = bp;
+    return bp;
+}
+
 // ---------------------------------------------------------------------------
 // a share of the targets (one GPU's force pass when the targets are split)
 
@@ -1716,6 +1841,50 @@ int32_t nbody_verlet_run_batched(double* pos, double* vel, const double* mass,
     P.dt = dt;
     P.part = at<double>(workspace, L.part);
     P.flags = at<uint32_t>(workspace, L.flags);
+    GroupShape gshape;
+    int gslots = 0;
+    if (batch_group_route(precision, offsets_host, num_systems, &gshape, &gslots)) {
+        GroupArgs A{};
+        A.pos_in = pos;
+        A.pos_out = pos;
+        A.vel = vel;
+        A.mass = mass;
+        if (precision != NBODY_FP64) {
+            NB_TRY(batched_split_prepare(pos, vel, mass, offsets_host, num_systems, G, small_mass,
+                                         workspace, L, s, &P));
+            A.pos_in = P.buf[0];
+            A.pos_out = P.buf[0];
+            A.vel = P.vel;
+            A.mass = P.mass;
+            A.nmaj = P.nmaj;
+        }
+        auto bp = batch_group_plan(offsets_host, num_systems, gshape, gslots);
+        GroupUnit* units = at<GroupUnit>(workspace, L.units);
+        // (the layout's bound covers it: at most n / 4 + ns units)
+        if (bp->group_units.size() * sizeof(GroupUnit) > L.bchunks - L.units)
+            return fail(NBODY_EUNSUPPORTED, "ensemble work list exceeds the workspace");
+        NB_HIP(hipMemcpyAsync(units, bp->group_units.data(),
+                              bp->group_units.size() * sizeof(GroupUnit), hipMemcpyHostToDevice,
+                              s));
+        A.units = units;
+        A.xbuf = P.part;
+        A.reg = reinterpret_cast<uint32_t*>(P.part + 12 * n);
+        A.flags = P.flags;
+        A.n = n;
+        A.stride = n;
+        A.G = G;
+        A.dt = dt;
+        A.steps = steps;
+        A.spread = 1;
+        NB_TRY(group_launches(precision, gshape, A, (int)bp->group_units.size(), bp->n_max,
+                              num_systems, steps, s));
+        if (precision != NBODY_FP64) {
+            const int32_t* perm = at<int32_t>(workspace, L.perm);
+            NB_HIP(launch_scatter(perm, n, P.buf[0], pos, 3, s));
+            NB_HIP(launch_scatter(perm, n, P.vel, vel, 3, s));
+        }
+        return NBODY_OK;
+    }
     NB_TRY(batched_plan_upload(offsets_host, num_systems,
                                batch_tile(precision, offsets_host, num_systems), workspace, L, s,
                                &P));

@@ -155,7 +155,8 @@ struct GroupArgs {
     int spread;             // one workgroup of every `spread` launched takes part
 };
 #define NB_GROUP_SHAPES(X)                                                            \
-    X(1, 8, 512) X(1, 4, 512) X(1, 4, 1024) X(2, 4, 512) X(3, 4, 1024) X(4, 4, 512)
+    X(1, 8, 512) X(1, 4, 512) X(1, 4, 1024) X(2, 4, 512) X(3, 4, 1024) X(4, 4, 512)    \
+    X(2, 8, 256) X(2, 16, 256) X(4, 8, 256)
 size_t group_lds_bytes(int64_t n, const GroupShape& g);
 // n_max: bodies of the largest system; words: exchange words to reset.
 hipError_t launch_group(int precision, const GroupShape& g, const GroupArgs& A, int blocks,

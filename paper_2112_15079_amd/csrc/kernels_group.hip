@@ -345,6 +345,7 @@ __global__ __launch_bounds__(NT) void k_group(GroupArgs A)
         body0 = u.body0;
         xoff = 12 * u.body0;
         n64 = u.n;
+        if (u.n == 0) return;   // (padding of the list)
     }
     const int n = (int)n64;
     const int groups = (n + Tw - 1) / Tw;

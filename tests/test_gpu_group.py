@@ -128,3 +128,43 @@ def test_beside_work_that_holds_the_gpu():
             nb.verlet_run(p, v, m, s.G, s.dt, 100)
     torch.cuda.synchronize()
     assert np.array_equal(H(p), want[0]) and np.array_equal(H(v), want[1])
+
+
+def ensemble(sizes, seed):
+    parts = [S.solar_system(seed + k, n - 11, n_major=10) if n > 11 else
+             S.System(*S.random_cluster(seed + k, n)) for k, n in enumerate(sizes)]
+    cat = lambda f: np.concatenate([f(x) for x in parts], axis=-1)
+    offs = np.concatenate([[0], np.cumsum(sizes)]).tolist()
+    return parts, offs, cat(lambda x: x.pos), cat(lambda x: x.vel), cat(lambda x: x.mass)
+
+
+# one system; sizes on either side of a workgroup's targets; systems spread over
+# all XCDs; every shape by total size (1,024, 4,096, 12,288 bodies); one
+# workgroup per system; more systems than workgroups fit at once
+ENSEMBLES = {
+    "one": [900], "tiny": [1, 2, 3, 4, 5, 33], "three": [239, 240, 241],
+    "4096": [31, 32, 33, 700, 1000, 1200], "12288": [2048, 2047, 500, 64, 65] + [300] * 12,
+    "small-many": [40 + (7 * k) % 361 for k in range(80)],
+    "large-many": [300 + (311 * k) % 1749 for k in range(20)],
+    "all-whole": [30 + k % 9 for k in range(1300)],
+}
+
+
+@pytest.mark.parametrize("precision,tol", [("fp64", 1e-12), ("split", 1e-10)])
+@pytest.mark.parametrize("name", list(ENSEMBLES))
+def test_ensembles_match_oracle_and_chain(name, precision, tol):
+    sizes = ENSEMBLES[name]
+    parts, offs, pos, vel, mass = ensemble(sizes, 80)
+    G, dt = S.G_AU_DAY_MSUN, 0.1
+    runs = []
+    for steps in ([9], [4, 1, 4]):
+        p, v = T(pos), T(vel)
+        for k in steps:
+            nb.verlet_run_batched(p, v, T(mass), offs, G, dt, k, precision=precision)
+        runs.append((H(p), H(v)))
+    assert np.array_equal(runs[0][0], runs[1][0]) and np.array_equal(runs[0][1], runs[1][1])
+    for k in {0, len(sizes) // 2, len(sizes) - 1, int(np.argmax(sizes))}:
+        a, b = offs[k], offs[k + 1]
+        pr, vr = oracle.verlet(parts[k].pos, parts[k].vel, parts[k].mass, G, dt, 9)
+        got = runs[0][0][:, a:b]
+        assert np.linalg.norm(got - pr) <= tol * np.linalg.norm(pr), (k, sizes[k])
