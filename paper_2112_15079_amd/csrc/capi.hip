@@ -257,12 +257,13 @@ int group_launches(int prec, const GroupShape& g, GroupArgs A, int blocks, int64
 
 // ... of a single system of n bodies, a run of `steps` steps with the state in
 // pos, vel (with traj the positions after each drift are stored and pos is only
-// read); or, with acc, the accelerations at pos.  xbuf: 12 n doubles, 16-byte
+// read); or, with acc, the accelerations at pos (body p's at acc_perm[p] if
+// given).  xbuf: 12 n doubles, 16-byte
 // aligned; reg: two words (both unused when last = 0).
 int group_run(int prec, const double* pos_in, double* pos_out, double* vel, const double* mass,
               int64_t n, const int64_t* nmaj, double G, double dt, int64_t last, int64_t steps,
               double* acc, double* traj, double* xbuf, uint32_t* reg, uint32_t* flags,
-              hipStream_t s)
+              hipStream_t s, const int32_t* acc_perm = nullptr)
 {
     GroupArgs A{};
     A.pos_in = pos_in;
@@ -273,6 +274,7 @@ int group_run(int prec, const double* pos_in, double* pos_out, double* vel, cons
     A.reg = reg;
     A.nmaj = nmaj;
     A.acc = acc;
+    A.acc_perm = acc_perm;
     A.traj = traj;
     A.flags = flags;
     A.n = n;
@@ -680,11 +682,23 @@ int run_steps(const StepPlan& P, int64_t steps, hipStream_t stream, bool use_gra
     return NBODY_OK;
 }
 
-int split_prepare(void* ws, const Layout& L, const double* mass, int64_t n, double small_mass,
-                  hipStream_t s)
+// The split form's working copies of one system, in class order.
+struct ClassOrdered {
+    const int32_t* perm;
+    const int64_t* nmaj;
+    double *pos, *vel, *mass, *gm;
+};
+
+int split_prepare(void* ws, const Layout& L, const double* pos, const double* vel,
+                  const double* mass, int64_t n, double G, double small_mass, hipStream_t s,
+                  ClassOrdered* c)
 {
-    NB_HIP(launch_partition(mass, nullptr, 1, n, small_mass, at<int32_t>(ws, L.perm),
-                            at<int64_t>(ws, L.nmaj), s));
+    int32_t* perm = at<int32_t>(ws, L.perm);
+    int64_t* nmaj = at<int64_t>(ws, L.nmaj);
+    *c = {perm, nmaj, at<double>(ws, L.pos_c), at<double>(ws, L.vel_c), at<double>(ws, L.mass_c),
+          at<double>(ws, L.gm)};
+    NB_HIP(launch_class_order(pos, vel, mass, nullptr, 1, n, n, small_mass, G, perm, nmaj, c->pos,
+                              c->vel, c->mass, c->gm, s));
     return NBODY_OK;
 }
 
@@ -773,8 +787,8 @@ int32_t nbody_accel(const double* pos, const double* vel, const double* mass, in
     const bool fused = tile.variant == 4;
     if (precision == NBODY_FP64) {
         if (group)
-            return group_run(0, pos, nullptr, nullptr, mass, n, nullptr, G, 0.0, 0, 0,
-                                  acc_out, nullptr, nullptr, nullptr, flags, s);
+            return group_run(0, pos, nullptr, nullptr, mass, n, nullptr, G, 0.0, 0, 0, acc_out,
+                             nullptr, nullptr, nullptr, flags, s);
         if (small) {
             NB_HIP(launch_run_small(0, tile, pos, nullptr, nullptr, mass, n, nullptr, G, 0.0, 0, 0,
                                     0, acc_out, nullptr, flags, s));
@@ -791,33 +805,25 @@ int32_t nbody_accel(const double* pos, const double* vel, const double* mass, in
                            kStoreAcc, flags, s));
         return NBODY_OK;
     }
-    NB_TRY(split_prepare(workspace, L, mass, n, small_mass, s));
-    const int32_t* perm = at<int32_t>(workspace, L.perm);
-    double* pos_c = at<double>(workspace, L.pos_c);
-    double* mass_c = at<double>(workspace, L.mass_c);
-    double* acc_c = at<double>(workspace, L.alt_c);
-    NB_HIP(launch_gather(perm, n, pos, pos_c, 3, s));
-    NB_HIP(launch_gather(perm, n, mass, mass_c, 1, s));
-    if (group) {
-        NB_TRY(group_run(precision, pos_c, nullptr, nullptr, mass_c, n,
-                              at<int64_t>(workspace, L.nmaj), G, 0.0, 0, 0, acc_c, nullptr,
-                              nullptr, nullptr, flags, s));
-    } else if (small) {
-        NB_HIP(launch_run_small(1, tile, pos_c, nullptr, nullptr, mass_c, n,
-                                at<int64_t>(workspace, L.nmaj), G, 0.0, 0, 0, 0, acc_c, nullptr,
-                                flags, s));
-    } else if (fused) {
-        NB_HIP(launch_scale(mass_c, G, n, gm, s));
-        NB_HIP(launch_step_fused(1, tile, pos_c, nullptr, nullptr, gm, n,
-                                 at<int64_t>(workspace, L.nmaj), 0.0, kStoreAcc, acc_c, flags, s));
-    } else {
-        NB_HIP(launch_scale(mass_c, G, n, gm, s));
-        NB_HIP(launch_force(precision, tile, pos_c, mass_c, gm, n, at<int64_t>(workspace, L.nmaj), G, part,
-                            s));
-        NB_HIP(launch_step(part, chunks, nullptr, n, nullptr, nullptr, nullptr, acc_c, 0.0,
-                           kStoreAcc, flags, s));
+    ClassOrdered c;
+    NB_TRY(split_prepare(workspace, L, pos, nullptr, mass, n, G, small_mass, s, &c));
+    if (group)
+        return group_run(precision, c.pos, nullptr, nullptr, c.mass, n, c.nmaj, G, 0.0, 0, 0,
+                         acc_out, nullptr, nullptr, nullptr, flags, s, c.perm);
+    if (!small && !fused) {
+        NB_HIP(launch_force(precision, tile, c.pos, c.mass, c.gm, n, c.nmaj, G, part, s));
+        NB_HIP(launch_step(part, chunks, nullptr, n, nullptr, nullptr, nullptr, acc_out, 0.0,
+                           kStoreAcc, flags, s, c.perm));
+        return NBODY_OK;
     }
-    NB_HIP(launch_scatter(perm, n, acc_c, acc_out, 3, s));
+    double* acc_c = at<double>(workspace, L.alt_c);
+    if (small)
+        NB_HIP(launch_run_small(1, tile, c.pos, nullptr, nullptr, c.mass, n, c.nmaj, G, 0.0, 0, 0,
+                                0, acc_c, nullptr, flags, s));
+    else
+        NB_HIP(launch_step_fused(1, tile, c.pos, nullptr, nullptr, c.gm, n, c.nmaj, 0.0, kStoreAcc,
+                                 acc_c, flags, s));
+    NB_HIP(launch_scatter(c.perm, n, acc_c, acc_out, nullptr, nullptr, s));
     return NBODY_OK;
 }
 
@@ -861,8 +867,8 @@ int verlet_run_on(double* pos, double* vel, const double* mass, int64_t n, doubl
     const bool small = P.tile.variant == 3;
     if (precision == NBODY_FP64) {
         if (group)
-            return group_run(0, pos, pos, vel, mass, n, nullptr, G, dt, steps, steps,
-                                  nullptr, nullptr, P.part, group_reg(P.flags), P.flags, s);
+            return group_run(0, pos, pos, vel, mass, n, nullptr, G, dt, steps, steps, nullptr,
+                             nullptr, P.part, group_reg(P.flags), P.flags, s);
         if (small) {
             NB_HIP(launch_run_small(0, P.tile, pos, pos, vel, mass, n, nullptr, G, dt, 0, steps,
                                     steps, nullptr, nullptr, P.flags, s));
@@ -881,36 +887,25 @@ int verlet_run_on(double* pos, double* vel, const double* mass, int64_t n, doubl
         if (steps & 1) NB_HIP(launch_scale(alt, 1.0, 3 * n, pos, s));
         return NBODY_OK;
     }
-    NB_TRY(split_prepare(ws, L, mass, n, small_mass, s));
-    const int32_t* perm = at<int32_t>(ws, L.perm);
-    double* pos_c = at<double>(ws, L.pos_c);
-    double* vel_c = at<double>(ws, L.vel_c);
-    double* mass_c = at<double>(ws, L.mass_c);
-    double* alt_c = at<double>(ws, L.alt_c);
-    NB_HIP(launch_gather(perm, n, pos, pos_c, 3, s));
-    NB_HIP(launch_gather(perm, n, vel, vel_c, 3, s));
-    NB_HIP(launch_gather(perm, n, mass, mass_c, 1, s));
-    P.nmaj = at<int64_t>(ws, L.nmaj);
-    if (group || small) {
-        if (group)
-            NB_TRY(group_run(precision, pos_c, pos_c, vel_c, mass_c, n, P.nmaj, G, dt,
-                                  steps, steps, nullptr, nullptr, P.part, group_reg(P.flags),
-                                  P.flags, s));
-        else
-            NB_HIP(launch_run_small(1, P.tile, pos_c, pos_c, vel_c, mass_c, n, P.nmaj, G, dt, 0,
-                                    steps, steps, nullptr, nullptr, P.flags, s));
-        NB_HIP(launch_scatter(perm, n, pos_c, pos, 3, s));
-        NB_HIP(launch_scatter(perm, n, vel_c, vel, 3, s));
-        return NBODY_OK;
+    ClassOrdered c;
+    NB_TRY(split_prepare(ws, L, pos, vel, mass, n, G, small_mass, s, &c));
+    const double* r_end = c.pos;
+    if (group) {
+        NB_TRY(group_run(precision, c.pos, c.pos, c.vel, c.mass, n, c.nmaj, G, dt, steps, steps,
+                         nullptr, nullptr, P.part, group_reg(P.flags), P.flags, s));
+    } else if (small) {
+        NB_HIP(launch_run_small(1, P.tile, c.pos, c.pos, c.vel, c.mass, n, c.nmaj, G, dt, 0, steps,
+                                steps, nullptr, nullptr, P.flags, s));
+    } else {
+        P.nmaj = c.nmaj;
+        P.mass = c.mass;
+        P.vel = c.vel;
+        P.buf[0] = c.pos;
+        P.buf[1] = at<double>(ws, L.alt_c);
+        NB_TRY(run_steps(P, steps, s, use_graph));
+        r_end = P.buf[steps & 1];
     }
-    NB_HIP(launch_scale(mass_c, G, n, gm, s));
-    P.mass = mass_c;
-    P.vel = vel_c;
-    P.buf[0] = pos_c;
-    P.buf[1] = alt_c;
-    NB_TRY(run_steps(P, steps, s, use_graph));
-    NB_HIP(launch_scatter(perm, n, P.buf[steps & 1], pos, 3, s));
-    NB_HIP(launch_scatter(perm, n, vel_c, vel, 3, s));
+    NB_HIP(launch_scatter(c.perm, n, r_end, pos, c.vel, vel, s));
     return NBODY_OK;
 }
 
@@ -1017,20 +1012,12 @@ int32_t nbody_rk4_run(double* pos, double* vel, const double* mass, int64_t n, d
         NB_HIP(launch_scale(mass, G, n, gm, s));
         return rk4_steps(P, pos, vel, rs, vs, sr, sv, steps, s);
     }
-    NB_TRY(split_prepare(workspace, L, mass, n, small_mass, s));
-    const int32_t* perm = at<int32_t>(workspace, L.perm);
-    double* pos_c = at<double>(workspace, L.pos_c);
-    double* vel_c = at<double>(workspace, L.vel_c);
-    double* mass_c = at<double>(workspace, L.mass_c);
-    NB_HIP(launch_gather(perm, n, pos, pos_c, 3, s));
-    NB_HIP(launch_gather(perm, n, vel, vel_c, 3, s));
-    NB_HIP(launch_gather(perm, n, mass, mass_c, 1, s));
-    NB_HIP(launch_scale(mass_c, G, n, gm, s));
-    P.mass = mass_c;
-    P.nmaj = at<int64_t>(workspace, L.nmaj);
-    NB_TRY(rk4_steps(P, pos_c, vel_c, rs, vs, sr, sv, steps, s));
-    NB_HIP(launch_scatter(perm, n, pos_c, pos, 3, s));
-    NB_HIP(launch_scatter(perm, n, vel_c, vel, 3, s));
+    ClassOrdered c;
+    NB_TRY(split_prepare(workspace, L, pos, vel, mass, n, G, small_mass, s, &c));
+    P.mass = c.mass;
+    P.nmaj = c.nmaj;
+    NB_TRY(rk4_steps(P, c.pos, c.vel, rs, vs, sr, sv, steps, s));
+    NB_HIP(launch_scatter(c.perm, n, c.pos, pos, c.vel, vel, s));
     return NBODY_OK;
 }
 
@@ -1199,7 +1186,7 @@ static int adjoint_core(const double* pos0, const double* vel0, const double* ma
     auto maybe_graph = [&](const GraphKey& key, int64_t kseg, auto&& body) -> int {
         return maybe_graph_on(s, key, kseg, body);
     };
-    NB_HIP(launch_scale(mass, G, n, gm, s));
+    if (!group) NB_HIP(launch_scale(mass, G, n, gm, s));
     if (forward) {
         NB_HIP(hipMemcpyAsync(ck_r(0), pos0, b3, hipMemcpyDeviceToDevice, s));
         NB_HIP(hipMemcpyAsync(ck_v(0), vel0, b3, hipMemcpyDeviceToDevice, s));
@@ -1597,22 +1584,16 @@ int batched_split_prepare(const double* pos, const double* vel, const double* ma
     int64_t* offs = at<int64_t>(ws, L.offs);
     NB_HIP(hipMemcpyAsync(offs, offsets_host, (ns + 1) * sizeof(int64_t), hipMemcpyHostToDevice, s));
     NB_HIP(hipStreamSynchronize(s));   // offsets_host may be released by the caller on return
-    NB_HIP(launch_partition(mass, offs, ns, 0, small_mass, at<int32_t>(ws, L.perm),
-                            at<int64_t>(ws, L.nmaj), s));
-    const int32_t* perm = at<int32_t>(ws, L.perm);
-    double* pos_c = at<double>(ws, L.pos_c);
-    double* vel_c = at<double>(ws, L.vel_c);
-    double* mass_c = at<double>(ws, L.mass_c);
-    double* gm = at<double>(ws, L.gm);
-    NB_HIP(launch_gather(perm, n, pos, pos_c, 3, s));
-    if (vel) NB_HIP(launch_gather(perm, n, vel, vel_c, 3, s));
-    NB_HIP(launch_gather(perm, n, mass, mass_c, 1, s));
-    NB_HIP(launch_scale(mass_c, G, n, gm, s));
-    P->mass = mass_c;
-    P->gm = gm;
-    P->vel = vel_c;
-    P->buf[0] = pos_c;
+    int64_t n_max = 0;
+    for (int32_t k = 0; k < ns; ++k) n_max = std::max(n_max, offsets_host[k + 1] - offsets_host[k]);
+    P->mass = at<double>(ws, L.mass_c);
+    P->gm = at<double>(ws, L.gm);
+    P->vel = at<double>(ws, L.vel_c);
+    P->buf[0] = at<double>(ws, L.pos_c);
     P->buf[1] = at<double>(ws, L.alt_c);
+    NB_HIP(launch_class_order(pos, vel, mass, offs, ns, n, n_max, small_mass, G,
+                              at<int32_t>(ws, L.perm), at<int64_t>(ws, L.nmaj), P->buf[0], P->vel,
+                              at<double>(ws, L.mass_c), at<double>(ws, L.gm), s));
     P->nmaj = at<int64_t>(ws, L.nmaj);
     return NBODY_OK;
 }
@@ -1880,8 +1861,7 @@ int32_t nbody_verlet_run_batched(double* pos, double* vel, const double* mass,
                               num_systems, steps, s));
         if (precision != NBODY_FP64) {
             const int32_t* perm = at<int32_t>(workspace, L.perm);
-            NB_HIP(launch_scatter(perm, n, P.buf[0], pos, 3, s));
-            NB_HIP(launch_scatter(perm, n, P.vel, vel, 3, s));
+            NB_HIP(launch_scatter(perm, n, P.buf[0], pos, P.vel, vel, s));
         }
         return NBODY_OK;
     }
@@ -1906,8 +1886,7 @@ int32_t nbody_verlet_run_batched(double* pos, double* vel, const double* mass,
                                  workspace, L, s, &P));
     const int32_t* perm = at<int32_t>(workspace, L.perm);
     NB_TRY(run_steps(P, steps, s, true));
-    NB_HIP(launch_scatter(perm, n, P.buf[steps & 1], pos, 3, s));
-    NB_HIP(launch_scatter(perm, n, P.vel, vel, 3, s));
+    NB_HIP(launch_scatter(perm, n, P.buf[steps & 1], pos, P.vel, vel, s));
     return NBODY_OK;
 }
 
@@ -2039,13 +2018,11 @@ int bench_prepare(int32_t kind, int32_t precision, const double* pos, const doub
     b->pos = pos;
     b->mass = mass;
     if (precision != NBODY_FP64) {
-        NB_TRY(split_prepare(workspace, L, mass, n, small_mass, s));
-        const int32_t* perm = at<int32_t>(workspace, L.perm);
-        NB_HIP(launch_gather(perm, n, pos, at<double>(workspace, L.pos_c), 3, s));
-        NB_HIP(launch_gather(perm, n, mass, at<double>(workspace, L.mass_c), 1, s));
-        b->pos = at<double>(workspace, L.pos_c);
-        b->mass = at<double>(workspace, L.mass_c);
-        b->nmaj = at<int64_t>(workspace, L.nmaj);
+        ClassOrdered c;
+        NB_TRY(split_prepare(workspace, L, pos, nullptr, mass, n, G, small_mass, s, &c));
+        b->pos = c.pos;
+        b->mass = c.mass;
+        b->nmaj = c.nmaj;
     }
     if (kind == 1) NB_HIP(launch_fill(b->scratch, 1e-3, 3 * n, s));   // cotangent for timing
     double* gm = at<double>(workspace, L.gm);

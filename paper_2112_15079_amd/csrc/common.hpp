@@ -147,6 +147,7 @@ struct GroupArgs {
     const GroupUnit* units; // NULL: one system of n bodies
     const int64_t* nmaj;    // split form
     double* acc;            // NULL or a(r)
+    const int32_t* acc_perm;   // NULL, or where each body's goes (one system)
     double* traj;           // NULL or the positions after each drift, 3 n a launch index
     uint32_t* flags;
     int64_t n, stride;      // bodies of the system (of all systems), plane stride
@@ -177,9 +178,11 @@ hipError_t launch_step_fused(int precision, const Tile& tile, const double* pos_
                              uint32_t* flags, hipStream_t s);
 // a_p = sum_{c < chunks_of(p)} part[c][.][p] in ascending c, then the mode's
 // updates.  chunks_of(p) = chunks, or body_chunks[p] when that is not NULL.
+// perm (NULL: none): accelerations are stored at perm[p] instead of p.
 hipError_t launch_step(const double* part, int chunks, const int8_t* body_chunks, int64_t n,
                        double* vel, const double* pos_in, double* pos_out, double* acc,
-                       double dt, int mode, uint32_t* flags, hipStream_t s);
+                       double dt, int mode, uint32_t* flags, hipStream_t s,
+                       const int32_t* perm = nullptr);
 // out[k * nt + q] = sum_{c < chunks} part[c][k][t0 + q] in ascending c, for
 // the targets t0 .. t0 + nt - 1 of an n-body system (a share of the targets).
 hipError_t launch_shard_sum(const double* part, int chunks, int64_t n, int64_t t0, int64_t nt,
@@ -195,17 +198,21 @@ hipError_t launch_rk4_stage(const double* part, int chunks, int64_t n, int stage
                             double* sv, uint32_t* flags, hipStream_t s);
 
 // ----- split form: class order -------------------------------------------------
-// Stable partition of each system's bodies into mass >= threshold first:
-// perm[body0 + i] = original index of the i-th body in class order, and
-// nmaj[k] = number of FP64-class bodies of system k.  offsets: device array of
-// num_systems + 1 body offsets, or NULL for one system of n_single bodies.
-hipError_t launch_partition(const double* mass, const int64_t* offsets, int num_systems,
-                            int64_t n_single, double threshold, int32_t* perm, int64_t* nmaj,
-                            hipStream_t s);
-hipError_t launch_gather(const int32_t* perm, int64_t n, const double* src3, double* dst3,
-                         int planes, hipStream_t s);
-hipError_t launch_scatter(const int32_t* perm, int64_t n, const double* src3, double* dst3,
-                          int planes, hipStream_t s);
+// Each system's bodies in class order, mass >= threshold first (stable):
+// perm[body0 + i] = original index of the i-th body in class order, nmaj[k] =
+// number of FP64-class bodies of system k, and the bodies themselves into
+// pos_c, vel_c (unless vel is NULL), mass_c and gm_c (G times the mass; planes of
+// stride n).  offsets: device array of num_systems + 1 body offsets, or NULL
+// for one system of n; n_max: bodies of the largest system.
+hipError_t launch_class_order(const double* pos, const double* vel, const double* mass,
+                              const int64_t* offsets, int num_systems, int64_t n, int64_t n_max,
+                              double threshold, double G, int32_t* perm, int64_t* nmaj,
+                              double* pos_c, double* vel_c, double* mass_c, double* gm_c,
+                              hipStream_t s);
+// Back to the original order: a[k n + perm[i]] = a_c[k n + i] for three planes
+// k, and b likewise (unless NULL).
+hipError_t launch_scatter(const int32_t* perm, int64_t n, const double* a_c, double* a,
+                          const double* b_c, double* b, hipStream_t s);
 
 // ----- diagnostics -------------------------------------------------------------
 // rows[p] = -G m_p / 2 sum_{j != p} m_j / |r_j - r_p| (compensated): source

@@ -193,7 +193,7 @@ __device__ __forceinline__ bool word_finish(const GroupArgs& A, const Word& w, i
         publish(w.slot + (cur == 2 ? 0 : cur + 1) * words, r);
     }
     if (w.comp == 3) return true;
-    if (A.acc) A.acc[w.e] = a;
+    if (A.acc) A.acc[A.acc_perm ? w.e - w.ep + A.acc_perm[w.ep] : w.e] = a;
     if (A.traj) A.traj[(i - A.i0) * 3 * A.n + w.e] = r;
     if (i == A.i1 && A.pos_out) A.pos_out[w.e] = r;
     if (A.steps > 0) A.vel[w.e] = v;

@@ -22,15 +22,18 @@ constexpr int kBlock = 256;
 // the epilogue reads is loaded before the partials, so its latency overlaps
 // theirs.
 // PER_BODY: an ensemble's per-body partial counts (body_chunks) instead of
-// one count for every body.
-template <int GS, bool PER_BODY>
+// one count for every body.  PERM: accelerations are stored at perm[p] (a
+// variant of its own: a step of 10,425 bodies took 0.24 us longer with the test).
+template <int GS, bool PER_BODY, bool PERM = false>
 __global__ __launch_bounds__(kBlock) void k_step(const double* __restrict__ part, int chunks,
                                                  const int8_t* __restrict__ body_chunks,
                                                  int64_t n, double* __restrict__ vel,
                                                  const double* __restrict__ pos_in,
                                                  double* __restrict__ pos_out,
-                                                 double* __restrict__ acc, double hdt, double dt,
-                                                 int mode, uint32_t* __restrict__ flags)
+                                                 double* __restrict__ acc,
+                                                 const int32_t* __restrict__ perm, double hdt,
+                                                 double dt, int mode,
+                                                 uint32_t* __restrict__ flags)
 {
     const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const int64_t i = t / GS;   // k * n + p
@@ -45,7 +48,7 @@ __global__ __launch_bounds__(kBlock) void k_step(const double* __restrict__ part
     const double a = chunk_sum<GS>(part, C, 3 * n, ii, sub, live);
     if (!head) return;
     bool finite = __builtin_isfinite(a);
-    if (mode & kStoreAcc) acc[i] = a;
+    if (mode & kStoreAcc) acc[PERM ? i - p + perm[p] : i] = a;
     if (mode & (kClose | kOpen)) {
         double v = v0;
         if (mode & kClose) v = v + hdt * a;
@@ -144,77 +147,105 @@ __global__ __launch_bounds__(kBlock) void k_rk4_stage(const double* __restrict__
     if (!finite && flags) atomicOr(flags, 1u);
 }
 
-__global__ __launch_bounds__(kBlock) void k_gather(const int32_t* __restrict__ perm, int64_t n,
-                                                   const double* __restrict__ src,
-                                                   double* __restrict__ dst, int planes)
-{
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    const int64_t j = perm[i];
-    for (int k = 0; k < planes; ++k) dst[(int64_t)k * n + i] = src[(int64_t)k * n + j];
-}
-
+// Back from class order: planes 0 .. 2 of a (and, from grid.y = 3 on, of b).
 __global__ __launch_bounds__(kBlock) void k_scatter(const int32_t* __restrict__ perm, int64_t n,
-                                                    const double* __restrict__ src,
-                                                    double* __restrict__ dst, int planes)
+                                                    const double* __restrict__ a_c,
+                                                    double* __restrict__ a,
+                                                    const double* __restrict__ b_c,
+                                                    double* __restrict__ b)
 {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= n) return;
-    const int64_t j = perm[i];
-    for (int k = 0; k < planes; ++k) dst[(int64_t)k * n + j] = src[(int64_t)k * n + i];
+    const int k = blockIdx.y;
+    if (k < 3) a[(int64_t)k * n + perm[i]] = a_c[(int64_t)k * n + i];
+    else       b[(int64_t)(k - 3) * n + perm[i]] = b_c[(int64_t)(k - 3) * n + i];
 }
 
-// Stable partition of each system into mass >= thr first (one workgroup per
-// system): a count pass, then a block-wide scan per 1024-body slice.
+// Class order (split form), one launch: workgroup (x, y) places slice x of
+// system y.  It counts the system's heavy bodies itself, before its slice
+// and in all, instead of waiting for the other slices' counts (8 n bytes read
+// from L2 per workgroup: 2 us at 10,425 bodies, where one workgroup that scans
+// slice after slice took 23 us and three gathers and a scale followed it);
+// within the slice, ranks come from wave ballots.
 constexpr int kPart = 1024;
 
-__global__ __launch_bounds__(kPart) void k_partition(const double* __restrict__ mass,
-                                                     const int64_t* __restrict__ offsets,
-                                                     int64_t n_single, double thr,
-                                                     int32_t* __restrict__ perm,
-                                                     int64_t* __restrict__ nmaj)
+struct ClassOrder {
+    const double* pos;
+    const double* vel;
+    const double* mass;
+    const int64_t* offsets;
+    int64_t n;          // plane stride (all systems' bodies)
+    double threshold, G;
+    int32_t* perm;
+    int64_t* nmaj;
+    double *pos_c, *vel_c, *mass_c, *gm_c;
+};
+
+__global__ __launch_bounds__(kPart) void k_class_order(ClassOrder P)
 {
-    __shared__ int scan[kPart];
+    constexpr int NW = kPart / 64;
+    __shared__ int s_before[NW], s_all[NW], s_wave[2][NW];
     const int tid = threadIdx.x;
-    const int64_t b0 = offsets ? offsets[blockIdx.x] : 0;
-    const int64_t b1 = offsets ? offsets[blockIdx.x + 1] : n_single;
+    const int lane = tid & 63;
+    const int w = tid >> 6;
+    const int64_t b0 = P.offsets ? P.offsets[blockIdx.y] : 0;
+    const int64_t b1 = P.offsets ? P.offsets[blockIdx.y + 1] : P.n;
+    const int64_t per = ((b1 - b0 + gridDim.x - 1) / gridDim.x + kPart - 1) / kPart * kPart;
+    const int64_t s0 = b0 + blockIdx.x * per;
+    const int64_t s1 = s0 + per < b1 ? s0 + per : b1;
+    if (s0 >= b1) return;
 
-    int cnt = 0;
-    for (int64_t i = b0 + tid; i < b1; i += kPart) cnt += (mass[i] >= thr) ? 1 : 0;
-    scan[tid] = cnt;
-    __syncthreads();
-    for (int w = kPart / 2; w > 0; w >>= 1) {
-        if (tid < w) scan[tid] += scan[tid + w];
-        __syncthreads();
+    int before = 0, all = 0;
+    for (int64_t i = b0 + tid; i < b1; i += kPart) {
+        const int f = P.mass[i] >= P.threshold ? 1 : 0;
+        all += f;
+        before += i < s0 ? f : 0;
     }
-    const int64_t total = scan[0];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        before += __shfl_xor(before, o, 64);
+        all += __shfl_xor(all, o, 64);
+    }
+    if (lane == 0) {
+        s_before[w] = before;
+        s_all[w] = all;
+    }
     __syncthreads();
+    int64_t major = 0, total = 0;
+    for (int k = 0; k < NW; ++k) {
+        major += s_before[k];
+        total += s_all[k];
+    }
+    if (blockIdx.x == 0 && tid == 0) P.nmaj[blockIdx.y] = total;
+    int64_t small = total + (s0 - b0) - major;   // next place of each class
 
-    int64_t base_major = 0, base_small = total;
-    for (int64_t c0 = b0; c0 < b1; c0 += kPart) {
+    int buf = 0;
+    for (int64_t c0 = s0; c0 < s1; c0 += kPart, buf ^= 1) {
         const int64_t i = c0 + tid;
-        const bool valid = i < b1;
-        const int f = (valid && mass[i] >= thr) ? 1 : 0;
-        scan[tid] = f;
-        __syncthreads();
-        for (int off = 1; off < kPart; off <<= 1) {
-            const int v = tid >= off ? scan[tid - off] : 0;
-            __syncthreads();
-            scan[tid] += v;
-            __syncthreads();
+        const bool valid = i < s1;
+        const double m = valid ? P.mass[i] : 0.0;
+        const bool f = valid && m >= P.threshold;
+        const uint64_t mask = __ballot(f);
+        if (lane == 0) s_wave[buf][w] = __popcll(mask);
+        __syncthreads();   // (the next round writes the other buffer)
+        int rank = __popcll(mask & (((uint64_t)1 << lane) - 1)), sum = 0;
+        for (int k = 0; k < NW; ++k) {
+            const int c = s_wave[buf][k];
+            rank += k < w ? c : 0;
+            sum += c;
         }
-        const int excl = scan[tid] - f;          // majors before tid in this slice
-        const int chunk_major = scan[kPart - 1];
         if (valid) {
-            if (f) perm[b0 + base_major + excl] = (int32_t)i;
-            else   perm[b0 + base_small + (tid - excl)] = (int32_t)i;
+            const int64_t o = b0 + (f ? major + rank : small + (tid - rank));
+            P.perm[o] = (int32_t)i;
+            P.mass_c[o] = m;
+            P.gm_c[o] = P.G * m;
+            for (int k = 0; k < 3; ++k) P.pos_c[k * P.n + o] = P.pos[k * P.n + i];
+            if (P.vel)
+                for (int k = 0; k < 3; ++k) P.vel_c[k * P.n + o] = P.vel[k * P.n + i];
         }
-        const int64_t nvalid = (b1 - c0 < kPart) ? (b1 - c0) : kPart;
-        base_major += chunk_major;
-        base_small += nvalid - chunk_major;
-        __syncthreads();
+        major += sum;
+        small += (s1 - c0 < kPart ? s1 - c0 : kPart) - sum;
     }
-    if (tid == 0) nmaj[blockIdx.x] = total;
 }
 
 // ---------------------------------------------------------------------------
@@ -380,24 +411,24 @@ static inline unsigned blocks_for(int64_t n, int b) { return (unsigned)((n + b -
 
 hipError_t launch_step(const double* part, int chunks, const int8_t* body_chunks, int64_t n,
                        double* vel, const double* pos_in, double* pos_out, double* acc,
-                       double dt, int mode, uint32_t* flags, hipStream_t s)
+                       double dt, int mode, uint32_t* flags, hipStream_t s, const int32_t* perm)
 {
     // four threads per element for 16 to 95 partials of a single system; one
     // below that, from 96 partials (the each-pair-once pass on large systems)
     // and for an ensemble's per-body counts, where each load of a wavefront
     // then reads 512 contiguous bytes of one partial plane (measured faster)
-    if (body_chunks)
-        hipLaunchKernelGGL((k_step<1, true>), dim3(blocks_for(3 * n, kBlock)), dim3(kBlock), 0, s,
-                           part, chunks, body_chunks, n, vel, pos_in, pos_out, acc, 0.5 * dt, dt,
-                           mode, flags);
-    else if (chunks >= 16 && chunks < 96)
-        hipLaunchKernelGGL((k_step<4, false>), dim3(blocks_for(12 * n, kBlock)), dim3(kBlock), 0,
-                           s, part, chunks, body_chunks, n, vel, pos_in, pos_out, acc, 0.5 * dt,
-                           dt, mode, flags);
-    else
-        hipLaunchKernelGGL((k_step<1, false>), dim3(blocks_for(3 * n, kBlock)), dim3(kBlock), 0,
-                           s, part, chunks, body_chunks, n, vel, pos_in, pos_out, acc, 0.5 * dt,
-                           dt, mode, flags);
+    const double hdt = 0.5 * dt;
+#define NB_STEP(GS, PER_BODY, PERM)                                                         \
+    hipLaunchKernelGGL((k_step<GS, PER_BODY, PERM>), dim3(blocks_for(3 * GS * n, kBlock)),  \
+                       dim3(kBlock), 0, s, part, chunks, body_chunks, n, vel, pos_in, pos_out, \
+                       acc, perm, hdt, dt, mode, flags)
+    const bool four = chunks >= 16 && chunks < 96;
+    if (body_chunks) NB_STEP(1, true, false);
+    else if (perm && four) NB_STEP(4, false, true);
+    else if (perm) NB_STEP(1, false, true);
+    else if (four) NB_STEP(4, false, false);
+    else NB_STEP(1, false, false);
+#undef NB_STEP
     return hipGetLastError();
 }
 
@@ -427,28 +458,26 @@ hipError_t launch_rk4_stage(const double* part, int chunks, int64_t n, int stage
     return hipGetLastError();
 }
 
-hipError_t launch_partition(const double* mass, const int64_t* offsets, int num_systems,
-                            int64_t n_single, double threshold, int32_t* perm, int64_t* nmaj,
-                            hipStream_t s)
+hipError_t launch_class_order(const double* pos, const double* vel, const double* mass,
+                              const int64_t* offsets, int num_systems, int64_t n, int64_t n_max,
+                              double threshold, double G, int32_t* perm, int64_t* nmaj,
+                              double* pos_c, double* vel_c, double* mass_c, double* gm_c,
+                              hipStream_t s)
 {
-    hipLaunchKernelGGL(k_partition, dim3((unsigned)num_systems), dim3(kPart), 0, s, mass, offsets,
-                       n_single, threshold, perm, nmaj);
+    // slices of 1,024 bodies, fewer and longer ones for large systems
+    const int64_t slices = (n_max + kPart - 1) / kPart;
+    const dim3 grid((unsigned)(slices < 1024 ? slices : 1024), (unsigned)num_systems);
+    const ClassOrder P{pos, vel, mass, offsets, n, threshold, G, perm, nmaj,
+                       pos_c, vel_c, mass_c, gm_c};
+    hipLaunchKernelGGL(k_class_order, grid, dim3(kPart), 0, s, P);
     return hipGetLastError();
 }
 
-hipError_t launch_gather(const int32_t* perm, int64_t n, const double* src, double* dst,
-                         int planes, hipStream_t s)
+hipError_t launch_scatter(const int32_t* perm, int64_t n, const double* a_c, double* a,
+                          const double* b_c, double* b, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_gather, dim3(blocks_for(n, kBlock)), dim3(kBlock), 0, s, perm, n, src,
-                       dst, planes);
-    return hipGetLastError();
-}
-
-hipError_t launch_scatter(const int32_t* perm, int64_t n, const double* src, double* dst,
-                          int planes, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_scatter, dim3(blocks_for(n, kBlock)), dim3(kBlock), 0, s, perm, n, src,
-                       dst, planes);
+    hipLaunchKernelGGL(k_scatter, dim3(blocks_for(n, kBlock), b ? 6 : 3), dim3(kBlock), 0, s,
+                       perm, n, a_c, a, b_c, b);
     return hipGetLastError();
 }
 
