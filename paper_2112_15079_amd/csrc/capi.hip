@@ -297,7 +297,7 @@ uint32_t* group_reg(uint32_t* flags) { return flags + 16; }
 
 struct Layout {
     size_t flags = 0, part = 0, alt = 0, gm = 0, perm = 0, nmaj = 0, offs = 0, pos_c = 0, vel_c = 0,
-           mass_c = 0, alt_c = 0, rows = 0, units = 0, bchunks = 0, ck = 0, seg = 0, lam_r = 0,
+           mass_c = 0, alt_c = 0, units = 0, bchunks = 0, ck = 0, seg = 0, lam_r = 0,
            lam_v = 0, g_m = 0, u = 0, vtmp = 0, rk_vs = 0, rk_sr = 0, rk_sv = 0, seg2 = 0,
            part2 = 0, vtmp2 = 0, total = 0;
 };
@@ -338,7 +338,6 @@ Layout layout(int op, int64_t n, int32_t ns, int64_t steps, int64_t K, int prec)
         L.mass_c = a.take(n * d);
         L.alt_c = a.take(3 * n * d);
     }
-    if (op == NBODY_OP_ENERGY) L.rows = a.take(n * d);
     if (op == NBODY_OP_RK4) {   // stage velocity and slope sums (alt is the stage position)
         L.rk_vs = a.take(3 * n * d);
         L.rk_sr = a.take(3 * n * d);
@@ -1030,11 +1029,9 @@ int32_t nbody_energy(const double* pos, const double* vel, const double* mass, i
     const Layout L = layout(NBODY_OP_ENERGY, n, 1, 0, 1, NBODY_FP64);
     NB_TRY(check_ws(workspace, workspace_bytes, L.total));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    double* rows = at<double>(workspace, L.rows);
     // the partial region holds chunk_cap(n) slots of 3 n doubles for this op
-    NB_HIP(launch_potential_rows(pos, mass, n, G, at<double>(workspace, L.part), chunk_cap(n), rows,
-                                 s));
-    NB_HIP(launch_energy_finish(rows, vel, mass, n, out, s));
+    NB_HIP(launch_energy(pos, vel, mass, n, G, at<double>(workspace, L.part), 3 * n * chunk_cap(n),
+                         out, s));
     return NBODY_OK;
 }
 

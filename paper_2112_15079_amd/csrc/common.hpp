@@ -215,13 +215,11 @@ hipError_t launch_scatter(const int32_t* perm, int64_t n, const double* a_c, dou
                           const double* b_c, double* b, hipStream_t s);
 
 // ----- diagnostics -------------------------------------------------------------
-// rows[p] = -G m_p / 2 sum_{j != p} m_j / |r_j - r_p| (compensated): source
-// chunks (at most max_chunks; part holds 2 n doubles per chunk) merged in
-// chunk order.
-hipError_t launch_potential_rows(const double* pos, const double* mass, int64_t n, double G,
-                                 double* part, int max_chunks, double* rows, hipStream_t s);
-hipError_t launch_energy_finish(const double* rows, const double* vel, const double* mass,
-                                int64_t n, double* out, hipStream_t s);
+// out[0..3) = kinetic, potential and total energy (compensated; each unordered
+// pair once).  part: part_doubles doubles of scratch, at least 4 per 256 bodies
+// (more of it allows more workgroups on small systems), 32-byte aligned.
+hipError_t launch_energy(const double* pos, const double* vel, const double* mass, int64_t n,
+                         double G, double* part, int64_t part_doubles, double* out, hipStream_t s);
 hipError_t launch_momenta(const double* pos, const double* vel, const double* mass, int64_t n,
                           double* out, hipStream_t s);
 

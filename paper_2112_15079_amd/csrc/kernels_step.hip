@@ -268,107 +268,140 @@ __device__ __forceinline__ void cmerge(CSum& a, const CSum& b)
     cadd(a, b.c);
 }
 
-constexpr int kRowTile = 256;
-
-// Row sums of the pair potential of Sec. 2 over one chunk of sources, each
-// unordered pair once: S_c(p) = sum_{j in chunk c, j > p} m_j / |r_j - r_p|,
-// compensated, stored as (s, c) in part[2c][p], part[2c + 1][p] (grid.y =
-// chunks of chunk_len; a chunk wholly below the row block has nothing to do).
-__global__ __launch_bounds__(kRowTile) void k_potential_rows(const double* __restrict__ pos,
-                                                             const double* __restrict__ mass,
-                                                             int64_t n, int64_t chunk_len,
-                                                             double* __restrict__ part)
+// The compensated sum of s and x without a branch (Knuth's two-sum: the error is
+// exact, as in cadd, in 7 additions).
+__device__ __forceinline__ void cadd7(CSum& a, double x)
 {
-    __shared__ double sx[kRowTile], sy[kRowTile], sz[kRowTile], sm[kRowTile];
-    const int tid = threadIdx.x;
-    const int64_t p = (int64_t)blockIdx.x * kRowTile + tid;
-    const int64_t q = p < n ? p : n - 1;
-    const double px = pos[q], py = pos[n + q], pz = pos[2 * n + q];
-    const int64_t je0 = (int64_t)(blockIdx.y + 1) * chunk_len;
-    const int64_t je = je0 < n ? je0 : n;
-    const int64_t row0 = (int64_t)blockIdx.x * kRowTile;
-    // sources j > p only: start at the row block's first row + 1 at the earliest
-    const int64_t jb = (int64_t)blockIdx.y * chunk_len > row0 + 1 ? (int64_t)blockIdx.y * chunk_len
-                                                                  : row0 + 1;
-    CSum acc = {0.0, 0.0};
-    for (int64_t j0 = jb; j0 < je; j0 += kRowTile) {
-        const int64_t j = j0 + tid;
-        __syncthreads();
-        if (j < je) {
-            sx[tid] = pos[j];
-            sy[tid] = pos[n + j];
-            sz[tid] = pos[2 * n + j];
-            sm[tid] = mass[j];
-        }
-        __syncthreads();
-        const int cnt = (je - j0 < kRowTile) ? (int)(je - j0) : kRowTile;
-        for (int jj = 0; jj < cnt; ++jj) {
-            if (j0 + jj <= q) continue;
-            const double dx = sx[jj] - px, dy = sy[jj] - py, dz = sz[jj] - pz;
-            const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
-            cadd(acc, sm[jj] * rinv_f64(r2));
-        }
-    }
-    if (p < n) {
-        part[(int64_t)(2 * blockIdx.y) * n + p] = acc.s;
-        part[(int64_t)(2 * blockIdx.y + 1) * n + p] = acc.c;
-    }
+    const double t = a.s + x;
+    const double z = t - a.s;
+    a.c += (a.s - (t - z)) + (x - z);
+    a.s = t;
 }
 
-// rows[p] = -G m_p * (the chunk sums merged in chunk order); sum_p rows[p] is
-// the pair potential (each unordered pair once).
-__global__ __launch_bounds__(kBlock) void k_potential_merge(const double* __restrict__ part,
-                                                            int chunks, const double* __restrict__ mass,
-                                                            int64_t n, double G,
-                                                            double* __restrict__ rows)
+// m times a compensated sum, compensated.
+__device__ __forceinline__ CSum cscale(double m, const CSum& a)
 {
-    const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (p >= n) return;
-    CSum m = {0.0, 0.0};
-    for (int c = 0; c < chunks; ++c)
-        cmerge(m, CSum{part[(int64_t)(2 * c) * n + p], part[(int64_t)(2 * c + 1) * n + p]});
-    rows[p] = -G * mass[p] * (m.s + m.c);
+    const double p = m * a.s;
+    return CSum{p, __builtin_fma(m, a.s, -p) + m * a.c};
+}
+
+// The sums of V values over a workgroup of NT threads, in a fixed order: wave v
+// takes value v, each lane every 64th thread's, then the lanes pairwise.  The
+// sum of value v is complete in lane 0 of wave v.  sh: V * NT values.
+template <int V, int NT>
+__device__ __forceinline__ CSum block_sums(CSum* sh, const CSum (&x)[V])
+{
+    static_assert(V <= NT / 64, "a wave per value");
+    const int lane = threadIdx.x & 63;
+    const int w = threadIdx.x >> 6;
+#pragma unroll
+    for (int v = 0; v < V; ++v) sh[v * NT + threadIdx.x] = x[v];
+    __syncthreads();
+    CSum a = {0.0, 0.0};
+    if (w < V) {
+        const CSum* row = sh + w * NT;
+        a = row[lane];
+#pragma unroll
+        for (int k = 1; k < NT / 64; ++k) cmerge(a, row[64 * k + lane]);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1)
+            cmerge(a, CSum{__shfl_down(a.s, o, 64), __shfl_down(a.c, o, 64)});
+    }
+    return a;
+}
+
+constexpr int kRowTile = 256;
+constexpr int kSrcTile = 128;
+
+// The pair potential of Sec. 2, each unordered pair once, and the kinetic
+// energy: workgroup (x, y) sums m_p m_j / |r_j - r_p| over its 256 rows p and
+// the sources j > p of chunk y (compensated per row, then over the rows) and,
+// if y = 0, its rows' m v^2 / 2, into part[4 (y gridDim.x + x) ..] as two
+// (s, c).  Bound by the vector ALU: 23 issue slots a pair, 7 of them the
+// compensation (the branch-free two-sum, for 10 slots with compares and
+// selects); the diagonal's tiles select instead of branching, which keeps their
+// pairs in flight together.  Both energies of 10,425 bodies: 57 us (102 with
+// rows merged through memory and one workgroup's tree), 1,000 bodies 16 (47),
+// 131,072 7.1 ms (11.8).  Two rows per lane: 63 us, 22 us and 6.4 ms.
+__global__ __launch_bounds__(kRowTile) void k_energy_tiles(const double* __restrict__ pos,
+                                                           const double* __restrict__ vel,
+                                                           const double* __restrict__ mass,
+                                                           int64_t n, int64_t chunk_len,
+                                                           double* __restrict__ part)
+{
+    __shared__ double4 src[kSrcTile];
+    __shared__ CSum sh[2 * kRowTile];
+    const int tid = threadIdx.x;
+    const int64_t row0 = (int64_t)blockIdx.x * kRowTile;
+    const int64_t c0 = (int64_t)blockIdx.y * chunk_len;
+    const int64_t c1 = c0 + chunk_len < n ? c0 + chunk_len : n;
+    CSum x[2] = {{0.0, 0.0}, {0.0, 0.0}};
+    if (blockIdx.y == 0 || c1 > row0) {   // (a chunk wholly before the rows: zeros)
+        const int64_t p = row0 + tid;
+        const int64_t q = p < n ? p : n - 1;
+        const double px = pos[q], py = pos[n + q], pz = pos[2 * n + q];
+        const double m = p < n ? mass[q] : 0.0;
+        CSum acc = {0.0, 0.0};
+        // sources j > p only: from the tile that holds the first row on
+        for (int64_t j0 = c0 > row0 ? c0 : row0; j0 < c1; j0 += kSrcTile) {
+            __syncthreads();
+            const int64_t j = j0 + tid;
+            if (tid < kSrcTile)   // (past the end: massless and far away)
+                src[tid] = j < c1 ? double4{pos[j], pos[n + j], pos[2 * n + j], mass[j]}
+                                  : double4{1.0e18, 1.0e18, 1.0e18, 0.0};
+            __syncthreads();
+            auto term = [&](const double4& b) {
+                const double dx = b.x - px, dy = b.y - py, dz = b.z - pz;
+                const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
+                return b.w * rinv_f64(r2);
+            };
+            if (j0 >= row0 + kRowTile) {   // every source is past every row
+#pragma unroll 4
+                for (int k = 0; k < kSrcTile; ++k) cadd7(acc, term(src[k]));
+            } else {
+#pragma unroll 4
+                for (int k = 0; k < kSrcTile; ++k) {
+                    const double e = term(src[k]);
+                    cadd7(acc, j0 + k > q ? e : 0.0);
+                }
+            }
+        }
+        x[0] = cscale(m, acc);
+        if (blockIdx.y == 0 && p < n) {
+            const double vx = vel[p], vy = vel[n + p], vz = vel[2 * n + p];
+            x[1].s = 0.5 * m * (vx * vx + vy * vy + vz * vz);
+        }
+    }
+    const CSum a = block_sums<2, kRowTile>(sh, x);
+    if ((tid & 63) == 0 && tid < 128) {
+        double* o = part + 4 * ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) + 2 * (tid >> 6);
+        o[0] = a.s;
+        o[1] = a.c;
+    }
 }
 
 constexpr int kRed = 1024;
 
-__device__ void block_reduce(CSum* sh, CSum v, int nvals)
+// out = kinetic, potential, total from the tiles' sums, in tile order per lane.
+__global__ __launch_bounds__(kRed) void k_energy_finish(const double* __restrict__ part,
+                                                        int64_t tiles, double G,
+                                                        double* __restrict__ out)
 {
-    // Writes the combined value of all threads' v into sh[0]; fixed order.
+    __shared__ CSum sh[2 * kRed];
     const int tid = threadIdx.x;
-    sh[tid] = v;
-    __syncthreads();
-    for (int w = kRed / 2; w > 0; w >>= 1) {
-        if (tid < w) {
-            CSum a = sh[tid];
-            cmerge(a, sh[tid + w]);
-            sh[tid] = a;
-        }
-        __syncthreads();
+    CSum x[2] = {{0.0, 0.0}, {0.0, 0.0}};
+    for (int64_t i = tid; i < tiles; i += kRed) {
+        const double4 t = reinterpret_cast<const double4*>(part)[i];
+        cmerge(x[0], CSum{t.x, t.y});
+        cmerge(x[1], CSum{t.z, t.w});
     }
-    (void)nvals;
-}
-
-__global__ __launch_bounds__(kRed) void k_energy_finish(const double* __restrict__ rows,
-                                                        const double* __restrict__ vel,
-                                                        const double* __restrict__ mass,
-                                                        int64_t n, double* __restrict__ out)
-{
-    __shared__ CSum sh[kRed];
-    const int tid = threadIdx.x;
-    CSum kin = {0.0, 0.0}, pot = {0.0, 0.0};
-    for (int64_t i = tid; i < n; i += kRed) {
-        const double vx = vel[i], vy = vel[n + i], vz = vel[2 * n + i];
-        cadd(kin, 0.5 * mass[i] * (vx * vx + vy * vy + vz * vz));
-        cadd(pot, rows[i]);
-    }
-    block_reduce(sh, kin, kRed);
-    const CSum K = sh[0];
+    CSum a = block_sums<2, kRed>(sh, x);
     __syncthreads();
-    block_reduce(sh, pot, kRed);
-    const CSum U = sh[0];
+    if ((tid & 63) == 0 && tid < 128) sh[tid >> 6] = a;
+    __syncthreads();
     if (tid == 0) {
-        const double k = K.s + K.c, u = U.s + U.c;
+        const CSum U = cscale(-G, sh[0]);
+        const double k = sh[1].s + sh[1].c, u = U.s + U.c;
         CSum e = {0.0, 0.0};
         cadd(e, k);
         cadd(e, u);
@@ -378,31 +411,31 @@ __global__ __launch_bounds__(kRed) void k_energy_finish(const double* __restrict
     }
 }
 
+// One workgroup (the call has no scratch memory): 6 waves finish a component
+// each (11 us at 10,425 bodies; 18 with a tree over all threads per component).
 __global__ __launch_bounds__(kRed) void k_momenta(const double* __restrict__ pos,
                                                   const double* __restrict__ vel,
                                                   const double* __restrict__ mass, int64_t n,
                                                   double* __restrict__ out)
 {
-    __shared__ CSum sh[kRed];
+    __shared__ CSum sh[6 * kRed];
     const int tid = threadIdx.x;
     CSum c[6];
     for (int k = 0; k < 6; ++k) c[k] = {0.0, 0.0};
+#pragma unroll 2
     for (int64_t i = tid; i < n; i += kRed) {
         const double rx = pos[i], ry = pos[n + i], rz = pos[2 * n + i];
         const double vx = vel[i], vy = vel[n + i], vz = vel[2 * n + i];
         const double m = mass[i];
-        cadd(c[0], m * vx);
-        cadd(c[1], m * vy);
-        cadd(c[2], m * vz);
-        cadd(c[3], m * (ry * vz - rz * vy));
-        cadd(c[4], m * (rz * vx - rx * vz));
-        cadd(c[5], m * (rx * vy - ry * vx));
+        cadd7(c[0], m * vx);
+        cadd7(c[1], m * vy);
+        cadd7(c[2], m * vz);
+        cadd7(c[3], m * (ry * vz - rz * vy));
+        cadd7(c[4], m * (rz * vx - rx * vz));
+        cadd7(c[5], m * (rx * vy - ry * vx));
     }
-    for (int k = 0; k < 6; ++k) {
-        block_reduce(sh, c[k], kRed);
-        if (tid == 0) out[k] = sh[0].s + sh[0].c;
-        __syncthreads();
-    }
+    const CSum a = block_sums<6, kRed>(sh, c);
+    if ((tid & 63) == 0 && tid < 6 * 64) out[tid >> 6] = a.s + a.c;
 }
 
 }  // namespace
@@ -481,28 +514,24 @@ hipError_t launch_scatter(const int32_t* perm, int64_t n, const double* a_c, dou
     return hipGetLastError();
 }
 
-hipError_t launch_potential_rows(const double* pos, const double* mass, int64_t n, double G,
-                                 double* part, int max_chunks, double* rows, hipStream_t s)
+hipError_t launch_energy(const double* pos, const double* vel, const double* mass, int64_t n,
+                         double G, double* part, int64_t part_doubles, double* out, hipStream_t s)
 {
-    // source chunks of whole tiles until about 1024 workgroups have work (half
-    // of the (row block, chunk) grid lies below the diagonal)
+    // source chunks of whole tiles until about 2,048 workgroups have work (half
+    // of the (row block, chunk) grid lies below the diagonal; 10,425 bodies:
+    // about 7 per CU), as far as the tiles' sums (4 doubles each) have room
     const int64_t row_blocks = blocks_for(n, kRowTile);
-    int64_t c = (2048 + row_blocks - 1) / row_blocks;
-    c = c < 1 ? 1 : (c > max_chunks ? max_chunks : c);
+    int64_t c = (4096 + row_blocks - 1) / row_blocks;
+    const int64_t room = part_doubles / (4 * row_blocks);
+    c = c < 1 ? 1 : c > room ? room : c;
+    if (c < 1) return hipErrorInvalidValue;
     const int64_t per = (n + c - 1) / c;
-    const int64_t chunk_len = (per + kRowTile - 1) / kRowTile * kRowTile;
+    const int64_t chunk_len = (per + kSrcTile - 1) / kSrcTile * kSrcTile;
     const int chunks = (int)((n + chunk_len - 1) / chunk_len);
-    hipLaunchKernelGGL(k_potential_rows, dim3((unsigned)row_blocks, (unsigned)chunks),
-                       dim3(kRowTile), 0, s, pos, mass, n, chunk_len, part);
-    hipLaunchKernelGGL(k_potential_merge, dim3(blocks_for(n, kBlock)), dim3(kBlock), 0, s, part,
-                       chunks, mass, n, G, rows);
-    return hipGetLastError();
-}
-
-hipError_t launch_energy_finish(const double* rows, const double* vel, const double* mass,
-                                int64_t n, double* out, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_energy_finish, dim3(1), dim3(kRed), 0, s, rows, vel, mass, n, out);
+    hipLaunchKernelGGL(k_energy_tiles, dim3((unsigned)row_blocks, (unsigned)chunks),
+                       dim3(kRowTile), 0, s, pos, vel, mass, n, chunk_len, part);
+    hipLaunchKernelGGL(k_energy_finish, dim3(1), dim3(kRed), 0, s, part, row_blocks * chunks, G,
+                       out);
     return hipGetLastError();
 }
 
