@@ -289,8 +289,54 @@ int group_run(int prec, const double* pos_in, double* pos_out, double* vel, cons
 }
 
 // The registration words of a workspace: behind the flags word (two for the
-// caller's stream, two for the adjoint's second).
+// caller's stream, two for the adjoint's second, two for its reverse sweep).
 uint32_t* group_reg(uint32_t* flags) { return flags + 16; }
+
+// The shape of the reverse sweep for n bodies.  Up to 2,048 the positions are
+// held in LDS beside the cotangents (us per position at 131, 1,000 and 2,000
+// bodies: 2.9, 5.0 and 10.0, against 3.7, 5.6 and 10.5 read from the caches);
+// beyond them 512 threads with three to five targets each read them ahead
+// (12.0 against 14.3 at 2,079), where registers do not allow more threads.
+GroupVjpShape group_vjp_shape(int64_t n)
+{
+    if (n <= 256) return {1, 8, 512, true};
+    if (n <= 1024) return {1, 4, 1024, true};
+    if (n <= 2048) return {2, 4, 1024, true};
+    if (n <= 2560) return {5, 2, 512, false};
+    if (n <= 3072) return {3, 4, 512, false};
+    return {4, 4, 512, false};
+}
+
+// Whether the reverse sweep of segments of K steps takes the group kernel: the
+// sizes of the runs (forward, recompute and sweep, us per step, against the
+// product and its reduction beside the recompute: 6.5 and 14.9 at 131 bodies,
+// 11.8 and 31.6 at 1,000, 28.3 and 33.9 at 2,079, 51 and 58 at 3,500), unless
+// nbody_set_tile chose a tile for the product.  (One position alone would
+// be written where others still read.)
+bool group_vjp_route(int64_t n, int64_t K)
+{
+    if (n < kGroupMin || n > kGroupMax || K < 2) return false;
+    std::lock_guard<std::mutex> lk(g_mu);
+    auto it = g_tiles.find(std::make_tuple(1, (int)NBODY_FP64, size_class(n)));
+    return it == g_tiles.end() || !it->second.forced;
+}
+
+// Positions of one segment's reverse sweep, in launches of two to about
+// kGroupSegment of them.
+int group_sweep(GroupVjpArgs A, hipStream_t s)
+{
+    const GroupVjpShape g = group_vjp_shape(A.n);
+    A.spread = group_spread(A.n);
+    int64_t left = A.count;
+    for (int64_t pieces = (left + kGroupSegment - 1) / kGroupSegment; pieces > 0; --pieces) {
+        A.count = (left + pieces - 1) / pieces;
+        NB_HIP(launch_group_vjp(g, A, s));
+        A.k1 -= A.count - (A.last ? 1 : 0);
+        A.last = nullptr;
+        left -= A.count;
+    }
+    return NBODY_OK;
+}
 
 // ---------------------------------------------------------------------------
 // workspace layout
@@ -1223,12 +1269,18 @@ static int adjoint_core(const double* pos0, const double* vel0, const double* ma
     NB_HIP(hipMemcpyAsync(lam_r, grad_posT, b3, hipMemcpyDeviceToDevice, s));
     NB_HIP(hipMemcpyAsync(lam_v, grad_velT, b3, hipMemcpyDeviceToDevice, s));
     NB_HIP(launch_fill(g_m, 0.0, n, s));
-    if (steps > 0) {
+    // The group kernel's sweep does all positions of a segment in one launch (the
+    // closing half kick too).  It holds a workgroup on every CU, as the recompute
+    // does, so the two take turns on the caller's stream (side by side: 12.9
+    // against 12.4 us per step at 1,000 bodies, 29.7 against 28.6 at 2,079).
+    const bool group_rev = group_vjp_route(n, std::min(K, steps));
+    const bool overlap = !group_rev;
+    if (steps > 0 && !group_rev) {
         // closing half kick of the last step: v_T = v_{T-1/2} + dt/2 a(r_T)
         NB_HIP(launch_vjp(vt, ck_r(nck), mass, lam_v, 0.5 * dt, n, G, part, s));
         NB_HIP(launch_vjp_reduce(part, vchunks, n, lam_r, g_m, lam_v, dt, true, s));
     }
-    // Segments in reverse order, pipelined over two streams: the side stream
+    // Segments in reverse order, pipelined over two streams (overlap): the side stream
     // recomputes the positions of segment c - 1 (from its checkpoint, into the
     // other segment buffer, with its own partials and velocity) while the
     // caller's stream runs the reverse sweep of segment c.  Events order a
@@ -1239,20 +1291,20 @@ static int adjoint_core(const double* pos0, const double* vel0, const double* ma
     R.part = part2;
     double* segbuf[2] = {seg, seg2};
     bool freed_recorded[2] = {false, false};
-    auto recompute = [&](int64_t c) -> int {
+    auto recompute = [&](int64_t c, hipStream_t rs) -> int {
         const int b = (int)(c & 1);
         const int64_t kseg = std::min(K, steps - c * K);
         double* sg = segbuf[b];
-        if (freed_recorded[b]) NB_HIP(hipStreamWaitEvent(sb, side->freed[b], 0));
-        NB_HIP(hipMemcpyAsync(sg, ck_r(c), b3, hipMemcpyDeviceToDevice, sb));
-        NB_HIP(hipMemcpyAsync(vtmp2, ck_v(c), b3, hipMemcpyDeviceToDevice, sb));
+        if (overlap && freed_recorded[b]) NB_HIP(hipStreamWaitEvent(rs, side->freed[b], 0));
+        NB_HIP(hipMemcpyAsync(sg, ck_r(c), b3, hipMemcpyDeviceToDevice, rs));
+        NB_HIP(hipMemcpyAsync(vtmp2, ck_v(c), b3, hipMemcpyDeviceToDevice, rs));
         if (group) {
             // (the segment's positions r_{cK+1} .. r_{cK+kseg-1}, as below)
             if (kseg >= 2)
                 NB_TRY(group_run(0, sg, nullptr, vtmp2, mass, n, nullptr, G, dt, kseg - 2,
                                       kseg, nullptr, sg + 3 * n, part2, group_reg(flags) + 2,
-                                      flags, sb));
-        } else NB_TRY(maybe_graph_on(sb, key_of(3, kseg, 0, sg), kseg, [&](hipStream_t cs) -> int {
+                                      flags, rs));
+        } else NB_TRY(maybe_graph_on(rs, key_of(3, kseg, 0, sg), kseg, [&](hipStream_t cs) -> int {
             // positions r_{cK+1} .. r_{cK+kseg-1} of the segment into its slots
             if (small && kseg >= 2)
                 NB_HIP(launch_run_small(0, R.tile, sg, nullptr, vtmp2, mass, n, nullptr, G, dt, 0,
@@ -1263,15 +1315,32 @@ static int adjoint_core(const double* pos0, const double* vel0, const double* ma
             }
             return (int)NBODY_OK;
         }));
-        NB_HIP(hipEventRecord(side->ready[b], sb));
+        if (overlap) NB_HIP(hipEventRecord(side->ready[b], rs));
         return NBODY_OK;
     };
     auto sweep = [&](int64_t c) -> int {
         const int b = (int)(c & 1);
         const int64_t kseg = std::min(K, steps - c * K);
         const double* sg = segbuf[b];
-        NB_HIP(hipStreamWaitEvent(s, side->ready[b], 0));
-        NB_TRY(maybe_graph(key_of(4, kseg, c == 0, sg), kseg, [&](hipStream_t cs) -> int {
+        if (overlap) NB_HIP(hipStreamWaitEvent(s, side->ready[b], 0));
+        if (group_rev) {   // (two positions at least: K of them, or one and the last)
+            GroupVjpArgs A{};
+            A.seg = sg;
+            A.last = c == nck - 1 ? ck_r(nck) : nullptr;
+            A.mass = mass;
+            A.lam_r = lam_r;
+            A.lam_v = lam_v;
+            A.g_m = g_m;
+            A.xbuf = part;
+            A.reg = group_reg(flags) + 4;
+            A.n = n;
+            A.G = G;
+            A.dt = dt;
+            A.k1 = kseg - 1;
+            A.count = kseg + (A.last ? 1 : 0);
+            A.first = c == 0 ? 1 : 0;
+            NB_TRY(group_sweep(A, s));
+        } else NB_TRY(maybe_graph(key_of(4, kseg, c == 0, sg), kseg, [&](hipStream_t cs) -> int {
             for (int64_t k = kseg - 1; k >= 0; --k) {
                 const int64_t i = c * K + k;
                 // kick v_{i+1/2} = v_{i-1/2} + dt a(r_i)   (dt/2 for i = 0); the
@@ -1282,17 +1351,22 @@ static int adjoint_core(const double* pos0, const double* vel0, const double* ma
             }
             return (int)NBODY_OK;
         }));
-        NB_HIP(hipEventRecord(side->freed[b], s));
+        if (overlap) NB_HIP(hipEventRecord(side->freed[b], s));
         freed_recorded[b] = true;
         return NBODY_OK;
     };
-    if (nck > 0) {
+    if (!overlap) {
+        for (int64_t c = nck - 1; c >= 0; --c) {
+            NB_TRY(recompute(c, s));
+            NB_TRY(sweep(c));
+        }
+    } else if (nck > 0) {
         // the checkpoints (forward run, above) and G m come before any recompute
         NB_HIP(hipEventRecord(side->fwd, s));
         NB_HIP(hipStreamWaitEvent(sb, side->fwd, 0));
-        NB_TRY(recompute(nck - 1));
+        NB_TRY(recompute(nck - 1, sb));
         for (int64_t c = nck - 1; c >= 0; --c) {
-            if (c > 0) NB_TRY(recompute(c - 1));
+            if (c > 0) NB_TRY(recompute(c - 1, sb));
             NB_TRY(sweep(c));
         }
     }

@@ -163,6 +163,35 @@ size_t group_lds_bytes(int64_t n, const GroupShape& g);
 hipError_t launch_group(int precision, const GroupShape& g, const GroupArgs& A, int blocks,
                         int64_t n_max, int64_t words, int nsys, hipStream_t s);
 
+// The reverse sweep of one checkpoint segment (`count` >= 2 positions) in one
+// launch: position `last` first, if given (the run's closing half kick), then
+// slots k1, k1 - 1, ... of seg; slot 0 is the run's first position if `first`.
+struct GroupVjpArgs {
+    const double* seg;
+    const double* last;
+    const double* mass;
+    double* lam_r;
+    double* lam_v;
+    double* g_m;
+    double* xbuf;   // 12 words per body, 16-byte aligned
+    uint32_t* reg;  // 2 words
+    int64_t n;
+    double G, dt;
+    int64_t k1, count;
+    int first;
+    int spread;     // as in GroupArgs
+};
+// Its shape: held, with the positions in LDS too.
+struct GroupVjpShape {
+    int tpl, lanes, threads;
+    bool held;
+};
+#define NB_GROUP_VJP_SHAPES(X)                                                         \
+    X(1, 8, 512, true) X(1, 4, 1024, true) X(2, 4, 1024, true) X(5, 2, 512, false)     \
+    X(3, 4, 512, false) X(4, 4, 512, false)
+size_t group_vjp_lds_bytes(int64_t n, const GroupVjpShape& g);
+hipError_t launch_group_vjp(const GroupVjpShape& g, const GroupVjpArgs& A, hipStream_t s);
+
 // ----- step epilogue (Eqs. (3)-(4) as kick-drift-kick) -----------------------
 enum StepMode : int {
     kStoreAcc = 1,   // write a to acc

@@ -36,6 +36,7 @@
 // FP64, or (SPLIT, class order) heavy sources with one Newton step and light
 // ones in FP32, summed in blocks of at most 16 that are added in FP64.
 #include <atomic>
+#include <type_traits>
 
 #include "common.hpp"
 #include "pair_math.hpp"
@@ -503,6 +504,197 @@ __global__ __launch_bounds__(NT) void k_group(GroupArgs A)
     if (bad && A.flags) atomicOr(A.flags, 1u);
 }
 
+// Reverse sweep of one checkpoint segment in one launch: at each of its
+// positions, last to first, lam_r += c J^T lam_v and g_m += c M^T lam_v, then
+// (but at the run's first) lam_v += dt lam_r.  A product and its reduction per
+// position are bound by two kernel boundaries and the partials' round trip:
+// 9.5, 16 and 19 us at 131, 1,000 and 2,079 bodies, with the recompute beside
+// them; here 2.9, 5.0 and 12, of which 0.1, 1.3 and 6 are arithmetic.  The
+// exchange is the one above with lam_v (and the mass) in the place of the
+// position (and G m); the positions are known beforehand, so they are staged
+// ahead of the exchange: into LDS (HELD), or by each lane into registers, P
+// rounds at a time, where LDS does not hold both.
+template <int T, int TT, int NT, bool HELD>
+__global__ __launch_bounds__(NT) void k_group_vjp(GroupVjpArgs A)
+{
+    using D = GroupDims<T, TT, NT>;
+    constexpr int S = NT / TT;
+    constexpr int Tw = D::Tw;
+    constexpr int P = T == 1 ? 4 : 2;   // rounds whose loads go out together
+    extern __shared__ double4 body[];   // u, m [n], (HELD) x, y, z [3][n], row parts [4 Tw][RS]
+    const int tid = threadIdx.x;
+    if (A.spread > 1 && blockIdx.x % A.spread != 0) return;
+    const int n = (int)A.n;
+    const int planned = (int)gridDim.x / A.spread;
+    const int groups = (n + Tw - 1) / Tw;
+    int rank = 0, present = 1;
+    if (planned > 1 && !register_workgroup(A.reg, planned, rank, present)) return;
+
+    double* held = reinterpret_cast<double*>(body + n);
+    double* red = held + (HELD ? 3 * n : 0);
+    const double* lds = reinterpret_cast<const double*>(body);
+    for (int q = tid; q < n; q += NT)
+        body[q] = double4{A.lam_v[q], A.lam_v[n + q], A.lam_v[2 * n + q], A.mass[q]};
+    __syncthreads();
+
+    const int t0 = tid % TT;
+    const int s = tid / TT;
+    const int col = tid & 15;
+    const int row = tid >> 4;
+    const int xwords = 4 * n;
+    const int el = tid / D::LPE;   // the word that this lane finishes (3: of g_m)
+    const int etgt = el >> 2;
+    const int ecomp = el & 3;
+    const bool finisher = tid < D::E * D::LPE && tid % D::LPE == 0;
+    int budget = kPollBudget;
+    int cur = 0;   // i mod 3
+    for (int64_t i = 0; i < A.count; ++i) {
+        const bool closing = A.last && i == 0;
+        const int64_t k = A.k1 - (i - (A.last ? 1 : 0));   // slot of the position
+        const bool start = !closing && A.first && k == 0;
+        const double* rp = closing ? A.last : A.seg + k * 3 * A.n;
+        for (int vg = rank; vg < groups; vg += present) {
+            const int base = vg * Tw;
+            const int ep = base + etgt;
+            const bool mine = finisher && ep < n;
+            double* slot = A.xbuf + 4 * base + el;
+            double* acc = ecomp < 3 ? A.lam_r + (int64_t)ecomp * n + ep : A.g_m + ep;
+            const double old = mine ? *acc : 0.0;
+            // positions: held in LDS, or the first rounds' in registers.  The
+            // order is that of each_source: the bodies after the group's own targets,
+            // wrapping, then the targets.
+            const int own1 = base + Tw < n ? base + Tw : n;
+            const int full = (n - (own1 - base)) / S;
+            auto at = [&](int x) {
+                const unsigned a = (unsigned)x, b = (unsigned)(x - n);
+                return (int)(a < b ? a : b);
+            };
+            double nx[P], ny[P], nz[P];
+            int nj[P];
+            auto fetch = [&](int k0) {
+#pragma unroll
+                for (int u = 0; u < P; ++u) {
+                    const int j = k0 + u < full ? at(own1 + s + (k0 + u) * S) : 0;
+                    nj[u] = j;
+                    nx[u] = rp[j];
+                    ny[u] = rp[n + j];
+                    nz[u] = rp[2 * n + j];
+                }
+            };
+            if (!HELD)
+                fetch(0);
+            else if (vg == rank)
+                for (int q = tid; q < 3 * n; q += NT) held[q] = rp[q];
+            if (vg == rank && i > 0) {
+                const double* src = A.xbuf + cur * xwords;
+                for (int x0 = tid; x0 < 2 * n; x0 += D::kB * NT)
+                    gather_words<D::kB, NT>(src, x0, 2 * n, reinterpret_cast<double2*>(body),
+                                            budget);
+            }
+            if (vg == rank) __syncthreads();
+            if (mine && i > 1 && i + 1 < A.count)
+                __hip_atomic_store(slot + (cur == 0 ? 2 : cur - 1) * xwords,
+                                   __builtin_bit_cast(double, kSentinel), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            double tx[T], ty[T], tz[T], qm[T], ux[T], uy[T], uz[T], ox[T], oy[T], oz[T], og[T];
+            int64_t qid[T];
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const int p = base + t0 + t * TT;
+                const int q = p < n ? p : n - 1;
+                const double4 b = body[q];
+                const double* ps = HELD ? held : rp;
+                tx[t] = ps[q];
+                ty[t] = ps[n + q];
+                tz[t] = ps[2 * n + q];
+                qid[t] = p;
+                ux[t] = b.x;
+                uy[t] = b.y;
+                uz[t] = b.z;
+                qm[t] = b.w;
+                ox[t] = 0.0;
+                oy[t] = 0.0;
+                oz[t] = 0.0;
+                og[t] = 0.0;
+            }
+            const double* ps = HELD ? held : rp;
+            auto term = [&](auto mask, int j, double x, double y, double z) {
+                const double4 b = body[j];
+                vjp_pair<T, decltype(mask)::value>(x, y, z, b.w, b.x, b.y, b.z, j, tx, ty, tz, qm,
+                                                   ux, uy, uz, qid, ox, oy, oz, og);
+            };
+            if (HELD) {
+#pragma unroll P
+                for (int k0 = 0; k0 < full; ++k0) {
+                    const int j = at(own1 + s + k0 * S);
+                    term(std::false_type{}, j, ps[j], ps[n + j], ps[2 * n + j]);
+                }
+            } else {
+                for (int k0 = 0; k0 < full; k0 += P) {
+                    double bx[P], by[P], bz[P];
+                    int bj[P];
+#pragma unroll
+                    for (int u = 0; u < P; ++u) {
+                        bx[u] = nx[u];
+                        by[u] = ny[u];
+                        bz[u] = nz[u];
+                        bj[u] = nj[u];
+                    }
+                    fetch(k0 + P);
+#pragma unroll
+                    for (int u = 0; u < P; ++u)
+                        if (k0 + u < full) term(std::false_type{}, bj[u], bx[u], by[u], bz[u]);
+                }
+            }
+            for (int q = s + full * S; q < n; q += S) {
+                const int j = at(own1 + q);
+                term(std::true_type{}, j, ps[j], ps[n + j], ps[2 * n + j]);
+            }
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const double sx = row_sum<TT>(ox[t]);
+                const double sy = row_sum<TT>(oy[t]);
+                const double sz = row_sum<TT>(oz[t]);
+                const double sg = row_sum<TT>(og[t]);
+                if (col < TT) {
+                    const int x = t0 + t * TT;
+                    red[x * D::RS + row] = sx;
+                    red[(Tw + x) * D::RS + row] = sy;
+                    red[(2 * Tw + x) * D::RS + row] = sz;
+                    red[(3 * Tw + x) * D::RS + row] = sg;
+                }
+            }
+            __syncthreads();
+            if (tid < D::E * D::LPE) {
+                const double* rs = red + (ecomp * Tw + etgt) * D::RS + tid % D::LPE;
+                constexpr int M = D::NR / D::LPE;
+                double a4[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int m = 0; m < M; ++m) a4[m & 3] += rs[m * D::LPE];
+                double a = (a4[0] + a4[1]) + (a4[2] + a4[3]);
+                if (D::LPE >= 4) a += row_ror<14>(a);
+                if (D::LPE >= 2) a += row_ror<15>(a);
+                if (mine) {
+                    const double gc = A.G * (closing || start ? 0.5 * A.dt : A.dt);
+                    const double r = old + (ecomp < 3 ? gc : -gc) * a;
+                    double w = lds[4 * ep + ecomp];
+                    *acc = r;
+                    if (ecomp < 3 && !start) w = __builtin_fma(A.dt, r, w);
+                    if (i + 1 < A.count) {
+                        // the reset above has arrived before this word does
+                        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                        publish(slot + (cur == 2 ? 0 : cur + 1) * xwords, w);
+                    } else if (ecomp < 3) {
+                        A.lam_v[(int64_t)ecomp * n + ep] = w;
+                    }
+                }
+            }
+            if (groups > present) __syncthreads();   // red is written again
+        }
+        cur = cur == 2 ? 0 : cur + 1;
+    }
+}
+
 __global__ __launch_bounds__(256) void k_group_init(double* __restrict__ xbuf, int64_t words,
                                                     uint32_t* __restrict__ reg, int nreg)
 {
@@ -536,12 +728,23 @@ hipError_t launch_shape(const GroupArgs& A, int blocks, size_t lds, hipStream_t 
     return hipGetLastError();
 }
 
-hipError_t init_exchange(const GroupArgs& A, int64_t words, int nsys, hipStream_t s)
+template <int T, int TT, int NT, bool HELD>
+hipError_t launch_vjp_shape(const GroupVjpArgs& A, int blocks, size_t lds, hipStream_t s)
 {
-    if (A.i1 == A.i0) return hipSuccess;
+    static std::atomic<uint64_t> allowed{0};
+    const hipError_t e =
+        allow_lds(reinterpret_cast<const void*>(&k_group_vjp<T, TT, NT, HELD>), allowed);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_group_vjp<T, TT, NT, HELD>), dim3((unsigned)(blocks * A.spread)), dim3(NT), lds,
+                       s, A);
+    return hipGetLastError();
+}
+
+hipError_t init_exchange(double* xbuf, int64_t words, uint32_t* reg, int nsys, hipStream_t s)
+{
     const int64_t m = words > 2 * nsys ? words : 2 * nsys;
-    hipLaunchKernelGGL(k_group_init, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, A.xbuf,
-                       words, A.reg, 2 * nsys);
+    hipLaunchKernelGGL(k_group_init, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, xbuf,
+                       words, reg, 2 * nsys);
     return hipGetLastError();
 }
 
@@ -559,13 +762,38 @@ hipError_t launch_group(int precision, const GroupShape& g, const GroupArgs& A, 
     if (blocks < 1 || A.i1 < A.i0 || (precision == 1 && !A.nmaj)) return hipErrorInvalidValue;
     const size_t lds = group_lds_bytes(n_max, g);
     if (lds > (size_t)kMaxLds) return hipErrorInvalidValue;
-    const hipError_t e = init_exchange(A, words, nsys, s);
-    if (e != hipSuccess) return e;
+    if (A.i1 > A.i0) {
+        const hipError_t e = init_exchange(A.xbuf, words, A.reg, nsys, s);
+        if (e != hipSuccess) return e;
+    }
 #define NB_CASE(TT_, LL, NN)                                                                 \
     if (g.tpl == TT_ && g.lanes == LL && g.threads == NN)                                    \
         return precision == 0 ? launch_shape<TT_, LL, NN, false>(A, blocks, lds, s)          \
                               : launch_shape<TT_, LL, NN, true>(A, blocks, lds, s);
     NB_GROUP_SHAPES(NB_CASE)
+#undef NB_CASE
+    return hipErrorInvalidValue;
+}
+
+size_t group_vjp_lds_bytes(int64_t n, const GroupVjpShape& g)
+{
+    const int64_t tw = (int64_t)g.tpl * g.lanes;
+    return (size_t)((g.held ? 7 : 4) * n + 4 * tw * (g.threads / 16 + 1)) * sizeof(double);
+}
+
+hipError_t launch_group_vjp(const GroupVjpShape& g, const GroupVjpArgs& A, hipStream_t s)
+{
+    if (A.count < 2 || A.n < 1) return hipErrorInvalidValue;
+    const size_t lds = group_vjp_lds_bytes(A.n, g);
+    if (lds > (size_t)kMaxLds) return hipErrorInvalidValue;
+    const hipError_t e = init_exchange(A.xbuf, 12 * A.n, A.reg, 1, s);
+    if (e != hipSuccess) return e;
+    const int64_t tw = (int64_t)g.tpl * g.lanes;
+    const int blocks = (int)((A.n + tw - 1) / tw);
+#define NB_CASE(TT_, LL, NN, HH)                                                 \
+    if (g.tpl == TT_ && g.lanes == LL && g.threads == NN && g.held == HH)        \
+        return launch_vjp_shape<TT_, LL, NN, HH>(A, blocks, lds, s);
+    NB_GROUP_VJP_SHAPES(NB_CASE)
 #undef NB_CASE
     return hipErrorInvalidValue;
 }

@@ -1,8 +1,10 @@
-// Per-pair arithmetic shared by the force kernels: the FP64 r^-3 factor, the
-// split form's one-Newton-step factor, and Kahan's compensated addition.
+// Per-pair arithmetic shared by the kernels: the FP64 r^-3 factor, the split
+// form's one-Newton-step factor, the transpose-Jacobian term, and Kahan's
+// compensated addition.
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stdint.h>
 
 namespace nb {
 namespace pm {
@@ -57,6 +59,46 @@ static __device__ __forceinline__ double rinv_f64(double r2)
     const double y = __builtin_amdgcn_rsq(r2);
     const double e = __builtin_fma(-r2, y * y, 1.0);
     return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
+}
+
+// One source (position, mass, cotangent) of the transpose-Jacobian product
+// against the T targets of a lane: o += K(d) (m_q u_j - m_j u_q), og += u_j . d / |d|^3;
+// MASK: the pair is left out where source j is target qid[t] itself.
+template <int T, bool MASK>
+static __device__ __forceinline__ void vjp_pair(double sx, double sy, double sz, double sm, double sux,
+                                         double suy, double suz, int64_t j, const double (&qx)[T],
+                                         const double (&qy)[T], const double (&qz)[T],
+                                         const double (&qm)[T], const double (&ux)[T],
+                                         const double (&uy)[T], const double (&uz)[T],
+                                         const int64_t (&qid)[T], double (&ox)[T],
+                                         double (&oy)[T], double (&oz)[T], double (&og)[T])
+{
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const double dx = sx - qx[t];
+        const double dy = sy - qy[t];
+        const double dz = sz - qz[t];
+        const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
+        const double y = rinv_f64(r2);
+        const double y2 = y * y;
+        double i3 = y * y2;
+        double i5 = i3 * y2;
+        if (MASK) {
+            const bool self = (j == qid[t]);
+            i3 = self ? 0.0 : i3;
+            i5 = self ? 0.0 : i5;
+        }
+        const double wx = __builtin_fma(-sm, ux[t], qm[t] * sux);
+        const double wy = __builtin_fma(-sm, uy[t], qm[t] * suy);
+        const double wz = __builtin_fma(-sm, uz[t], qm[t] * suz);
+        const double dw = __builtin_fma(dz, wz, __builtin_fma(dy, wy, dx * wx));
+        const double c = 3.0 * dw * i5;
+        ox[t] = __builtin_fma(-c, dx, __builtin_fma(wx, i3, ox[t]));
+        oy[t] = __builtin_fma(-c, dy, __builtin_fma(wy, i3, oy[t]));
+        oz[t] = __builtin_fma(-c, dz, __builtin_fma(wz, i3, oz[t]));
+        const double ud = __builtin_fma(suz, dz, __builtin_fma(suy, dy, sux * dx));
+        og[t] = __builtin_fma(ud, i3, og[t]);
+    }
 }
 
 // Kahan's compensated addition: s + x with the rounding error carried in c.
