@@ -204,13 +204,23 @@ constexpr int64_t kGroupMax = 4095;
 // the chip's 256 CUs are used, one workgroup each (us per step at 1,000
 // bodies: 3.4 with 250 workgroups of 4 targets, 4.0 with 125 of 8), with two
 // waves per SIMD where a round's latency hides behind them (1,000 bodies: 3.4
-// with 1,024 threads, 3.7 with 512; 500 bodies: 2.6 and 2.5).
+// with 1,024 threads, 3.7 with 512; 500 bodies: 2.6 and 2.5).  Between 1,024 and
+// 2,560 bodies the targets per workgroup grow in steps of one to two, by three or
+// five lanes side by side (us per step, FP64 and split, against the next power
+// of two or twelve: 3.9 and 4.0 against 4.4 and 4.1 at 1,100; 7.4 and 6.6 against
+// 8.2 and 7.5 at 2,079; 8.8 and 7.9 against 9.3 and 8.3 at 2,500).  Above, their
+// idle lanes cost more than the finer steps give (14 targets against 12: 12.1
+// against 10.5 at 3,000; against 16: 13.8 and 13.8 at 3,500).
 GroupShape group_shape(int64_t n)
 {
     if (n <= 256) return {1, 8, 512};
     if (n <= 768) return {1, 4, 512};
     if (n <= 1024) return {1, 4, 1024};
+    if (n <= 1280) return {1, 5, 1024};
+    if (n <= 1536) return {2, 3, 512};
     if (n <= 2048) return {2, 4, 512};
+    if (n <= 2304) return {3, 3, 512};
+    if (n <= 2560) return {2, 5, 1024};
     if (n <= 3072) return {3, 4, 1024};
     return {4, 4, 512};
 }
@@ -301,6 +311,8 @@ GroupVjpShape group_vjp_shape(int64_t n)
 {
     if (n <= 256) return {1, 8, 512, true};
     if (n <= 1024) return {1, 4, 1024, true};
+    if (n <= 1280) return {1, 5, 1024, true};
+    if (n <= 1536) return {2, 3, 1024, true};
     if (n <= 2048) return {2, 4, 1024, true};
     if (n <= 2560) return {5, 2, 512, false};
     if (n <= 3072) return {3, 4, 512, false};

@@ -157,7 +157,8 @@ struct GroupArgs {
 };
 #define NB_GROUP_SHAPES(X)                                                            \
     X(1, 8, 512) X(1, 4, 512) X(1, 4, 1024) X(2, 4, 512) X(3, 4, 1024) X(4, 4, 512)    \
-    X(2, 8, 256) X(2, 16, 256) X(4, 8, 256)
+    X(2, 8, 256) X(2, 16, 256) X(4, 8, 256)                                           \
+    X(1, 5, 1024) X(2, 3, 512) X(3, 3, 512) X(2, 5, 1024)
 size_t group_lds_bytes(int64_t n, const GroupShape& g);
 // n_max: bodies of the largest system; words: exchange words to reset.
 hipError_t launch_group(int precision, const GroupShape& g, const GroupArgs& A, int blocks,
@@ -188,7 +189,7 @@ struct GroupVjpShape {
 };
 #define NB_GROUP_VJP_SHAPES(X)                                                         \
     X(1, 8, 512, true) X(1, 4, 1024, true) X(2, 4, 1024, true) X(5, 2, 512, false)     \
-    X(3, 4, 512, false) X(4, 4, 512, false)
+    X(3, 4, 512, false) X(4, 4, 512, false) X(1, 5, 1024, true) X(2, 3, 1024, true)
 size_t group_vjp_lds_bytes(int64_t n, const GroupVjpShape& g);
 hipError_t launch_group_vjp(const GroupVjpShape& g, const GroupVjpArgs& A, hipStream_t s);
 

@@ -93,10 +93,17 @@ __device__ __forceinline__ double row_ror(double x)
     return __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
 }
 
-// Sum over the lanes of a row whose column is equal modulo TT.
+// Sum over the slices of a row: lanes t, t + TT, ... of its first TT * (16 / TT),
+// complete in the lanes t < TT (in all lanes where TT divides 16).
 template <int TT>
 __device__ __forceinline__ double row_sum(double x)
 {
+    static_assert(16 % TT == 0 || TT == 3 || TT == 5, "lanes side by side");
+    if (TT == 5) return x + row_ror<16 - 5>(x) + row_ror<16 - 10>(x);
+    if (TT == 3) {
+        const double y = x + row_ror<16 - 6>(x);
+        return y + row_ror<16 - 3>(y) + row_ror<16 - 12>(x);
+    }
     if (TT <= 8) x += row_ror<8>(x);
     if (TT <= 4) x += row_ror<4>(x);
     if (TT <= 2) x += row_ror<2>(x);
@@ -312,7 +319,9 @@ __device__ __forceinline__ void each_source(int j0, int j1, int s, int own0, int
 }
 
 // T targets per lane, TT lanes side by side on different targets (Tw = T TT
-// targets per virtual group), NT threads, S = NT / TT source slices.  A body
+// targets per virtual group), NT threads, S source slices, 16 / TT in every row
+// of 16 lanes.  (TT = 3 or 5 leaves the row's last lane without work of its
+// own: it repeats the last slice.)  A body
 // is four words (x, y, z, G m) in LDS and in the exchange buffers alike, so
 // the exchange is a linear copy, and a virtual group of four targets has a
 // cache line of its own, which then changes hands once per step.
@@ -321,6 +330,7 @@ struct GroupDims {
     static constexpr int Tw = T * TT;
     static constexpr int E = 4 * Tw;                    // words of a virtual group
     static constexpr int NR = NT / 16;                  // rows of 16 lanes
+    static constexpr int S = NR * (16 / TT);
     static constexpr int LPE = E <= 16 ? 4 : (E <= 32 ? 2 : 1);   // finishing lanes per word
     static constexpr int RS = NR + 1;                   // LDS stride of a sum's row parts
     static constexpr int kB = T < 4 ? 4 * T : 16;       // 16-byte loads per thread in flight
@@ -331,7 +341,7 @@ template <int T, int TT, int NT, bool SPLIT>
 __global__ __launch_bounds__(NT) void k_group(GroupArgs A)
 {
     using D = GroupDims<T, TT, NT>;
-    constexpr int S = NT / TT;
+    constexpr int S = D::S;
     constexpr int Tw = D::Tw;
     constexpr int kUnroll = T == 1 ? 4 : (T == 2 ? 2 : 1);
     extern __shared__ double4 body[];   // [n], then the row parts [3 Tw][RS]
@@ -373,10 +383,10 @@ __global__ __launch_bounds__(NT) void k_group(GroupArgs A)
     }
     __syncthreads();
 
-    const int t0 = tid % TT;
-    const int s = tid / TT;
     const int col = tid & 15;
     const int row = tid >> 4;
+    const int t0 = col % TT;
+    const int s = row * (16 / TT) + (col / TT < 16 / TT ? col / TT : 16 / TT - 1);
     const int xwords = 4 * n;
     double* xb = A.xbuf + xoff;   // three buffers of xwords words
     const double hdt = 0.5 * A.dt;
@@ -518,7 +528,7 @@ template <int T, int TT, int NT, bool HELD>
 __global__ __launch_bounds__(NT) void k_group_vjp(GroupVjpArgs A)
 {
     using D = GroupDims<T, TT, NT>;
-    constexpr int S = NT / TT;
+    constexpr int S = D::S;
     constexpr int Tw = D::Tw;
     constexpr int P = T == 1 ? 4 : 2;   // rounds whose loads go out together
     extern __shared__ double4 body[];   // u, m [n], (HELD) x, y, z [3][n], row parts [4 Tw][RS]
@@ -537,10 +547,10 @@ __global__ __launch_bounds__(NT) void k_group_vjp(GroupVjpArgs A)
         body[q] = double4{A.lam_v[q], A.lam_v[n + q], A.lam_v[2 * n + q], A.mass[q]};
     __syncthreads();
 
-    const int t0 = tid % TT;
-    const int s = tid / TT;
     const int col = tid & 15;
     const int row = tid >> 4;
+    const int t0 = col % TT;
+    const int s = row * (16 / TT) + (col / TT < 16 / TT ? col / TT : 16 / TT - 1);
     const int xwords = 4 * n;
     const int el = tid / D::LPE;   // the word that this lane finishes (3: of g_m)
     const int etgt = el >> 2;

@@ -168,3 +168,9 @@ def test_ensembles_match_oracle_and_chain(name, precision, tol):
         pr, vr = oracle.verlet(parts[k].pos, parts[k].vel, parts[k].mass, G, dt, 9)
         got = runs[0][0][:, a:b]
         assert np.linalg.norm(got - pr) <= tol * np.linalg.norm(pr), (k, sizes[k])
+
+
+@pytest.mark.parametrize("precision,tol", [("fp64", 1e-13), ("split", 2e-12)])
+@pytest.mark.parametrize("n", [1280, 1281, 1536, 1537, 2304, 2305, 2560, 2561])
+def test_shapes_with_three_and_five_lanes_side_by_side(n, precision, tol):
+    test_shapes_match_oracle_and_chain(n, precision, tol)

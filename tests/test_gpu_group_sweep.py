@@ -50,3 +50,8 @@ def test_sweep_matches_one_product_per_position(n, steps, K):
     assert np.array_equal(a[3], b[3]) and np.array_equal(a[4], b[4])
     for x, y in zip(a, gradients(n, steps, K, False)):
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("n", [1280, 1281, 1536, 1537])
+def test_sweep_with_three_and_five_lanes_side_by_side(n):
+    test_sweep_matches_one_product_per_position(n, 7, 3)
