@@ -8,6 +8,7 @@ library is missing or no GPU is present, calls raise.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 import threading
 
@@ -131,8 +132,18 @@ def check(status: int, what: str) -> None:
     raise NBodyError(msg)
 
 
+def _index(device) -> int:
+    index = (device if isinstance(device, torch.device) else torch.device(device)).index
+    return torch.cuda.current_device() if index is None else index
+
+
+# The handle of a device's current stream, without the Stream object around it
+# (0.06 us against 1.8): a call of a small system is bound by its host time.
+_raw_stream = torch._C._cuda_getCurrentRawStream
+
+
 def stream_handle(device=None) -> int:
-    return torch.cuda.current_stream(device).cuda_stream
+    return _raw_stream(torch.cuda.current_device() if device is None else _index(device))
 
 
 # ----------------------------------------------------------------------------
@@ -149,19 +160,19 @@ def workspace(nbytes: int, device) -> torch.Tensor:
     order of its stream's work, the only stream that used it (the library's
     own second stream in the adjoint is ordered before the caller's stream
     returns)."""
-    dev = torch.device(device)
-    index = dev.index if dev.index is not None else torch.cuda.current_device()
-    key = (index, torch.cuda.current_stream(index).cuda_stream)
+    index = _index(device)
+    key = (index, _raw_stream(index))
     buf = _ws.get(key)
     if buf is None or buf.numel() < nbytes:
         with torch.cuda.device(index):
-            buf = torch.zeros(max(nbytes, 256), dtype=torch.uint8, device=dev)
+            buf = torch.zeros(max(nbytes, 256), dtype=torch.uint8, device=device)
         if buf.data_ptr() % 256:
             raise NBodyError("device allocation is not 256-byte aligned")
         _ws[key] = buf
     return buf
 
 
+@functools.lru_cache(maxsize=256, typed=True)   # (a function of the sizes alone)
 def workspace_bytes(op: int, n: int, num_systems: int = 1, steps: int = 0,
                     checkpoint_every: int = 1, precision: int = NBODY_FP64) -> int:
     b = load().nbody_workspace_bytes(op, n, num_systems, steps, checkpoint_every, precision)

@@ -35,13 +35,14 @@ def _prec(p) -> int:
 def _state(t: torch.Tensor, name: str, n: int | None = None, planes: int = 3) -> torch.Tensor:
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
-    if t.dtype != torch.float64:
+    if t.dtype is not torch.float64:
         raise TypeError(f"{name} must be float64, got {t.dtype}")
-    if t.device.type != "cuda":
+    if not t.is_cuda:
         raise ValueError(f"{name} must be on the GPU (no CPU path exists)")
-    want = (planes, n) if planes > 1 else (n,)
-    if n is not None and tuple(t.shape) != want:
-        raise ValueError(f"{name} must have shape {want}, got {tuple(t.shape)}")
+    if n is not None:
+        want = (planes, n) if planes > 1 else (n,)
+        if t.shape != want:
+            raise ValueError(f"{name} must have shape {want}, got {tuple(t.shape)}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
     return t
@@ -49,9 +50,10 @@ def _state(t: torch.Tensor, name: str, n: int | None = None, planes: int = 3) ->
 
 def _mass(mass: torch.Tensor) -> int:
     _state(mass, "mass", planes=1)
-    if mass.dim() != 1 or mass.shape[0] < 1:
+    n = mass.shape[0] if mass.dim() == 1 else 0
+    if n < 1:
         raise ValueError("mass must be a non-empty 1-D tensor")
-    return int(mass.shape[0])
+    return int(n)
 
 
 def _same_device(*ts):
@@ -76,7 +78,8 @@ def accel(pos, mass, G, precision="fp64", small_mass=None, out=None):
     p = _prec(precision)
     if out is None:
         out = torch.empty((3, n), dtype=torch.float64, device=dev)
-    _state(out, "out", n)
+    else:
+        _state(out, "out", n)
     lib = C.load()
     nb = C.workspace_bytes(C.OP_ACCEL, n, precision=p)
     ws = C.workspace(nb, dev)
