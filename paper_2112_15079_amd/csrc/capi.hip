@@ -121,7 +121,8 @@ bool mutual_fits(int kind, int prec, int64_t n)
 // each-pair-once pass may run.
 int part_slots(int64_t n)
 {
-    return std::max(chunk_cap(n), n <= kMutualMaxN ? mutual_slots(n, 4, 4) : 0);
+    if (n > kMutualMaxN) return chunk_cap(n);
+    return std::max({chunk_cap(n), mutual_slots(n, 4, 4), mutual_force_slots(NBODY_FP64, n, 4, 4)});
 }
 
 // Defaults from tile sweeps on MI355X (the autotuner refines them): one
@@ -835,7 +836,7 @@ int32_t nbody_accel(const double* pos, const double* vel, const double* mass, in
     NB_TRY(check_ws(workspace, workspace_bytes, L.total));
     hipStream_t s = static_cast<hipStream_t>(stream);
     const Tile tile = pick_tile(0, precision, n);
-    const int chunks = effective_chunks(n, tile);
+    const int chunks = force_slots(precision, n, tile);
     double* part = at<double>(workspace, L.part);
     uint32_t* flags = at<uint32_t>(workspace, L.flags);
     double* gm = at<double>(workspace, L.gm);
@@ -911,7 +912,7 @@ int verlet_run_on(double* pos, double* vel, const double* mass, int64_t n, doubl
     StepPlan P;
     P.prec = precision;
     P.tile = pick_tile(0, precision, n);
-    P.chunks = effective_chunks(n, P.tile);
+    P.chunks = force_slots(precision, n, P.tile);
     P.n = n;
     P.G = G;
     P.dt = dt;
@@ -1052,7 +1053,7 @@ int32_t nbody_rk4_run(double* pos, double* vel, const double* mass, int64_t n, d
     P.tile = pick_tile(0, precision, n);
     if (P.tile.variant == 3 || P.tile.variant == 4)   // whole-step variants
         P.tile = force_only_tile(precision, n);
-    P.chunks = effective_chunks(n, P.tile);
+    P.chunks = force_slots(precision, n, P.tile);
     P.n = n;
     P.G = G;
     P.dt = dt;
@@ -1204,7 +1205,7 @@ static int adjoint_core(const double* pos0, const double* vel0, const double* ma
     StepPlan P;
     P.prec = NBODY_FP64;
     P.tile = pick_tile(0, NBODY_FP64, n);
-    P.chunks = effective_chunks(n, P.tile);
+    P.chunks = force_slots(NBODY_FP64, n, P.tile);
     P.n = n;
     P.G = G;
     P.dt = dt;
@@ -2237,7 +2238,7 @@ int32_t nbody_autotune(int32_t kind, int32_t precision, const double* pos, const
                                      kStoreAcc, scratch, nullptr, s));
         } else if (kind == 0) {
             NB_HIP(launch_force(precision, t, pos_w, mass_w, b.gm, n, nmaj, G, part, s));
-            NB_HIP(launch_step(part, effective_chunks(n, t), nullptr, n, nullptr, nullptr,
+            NB_HIP(launch_step(part, force_slots(precision, n, t), nullptr, n, nullptr, nullptr,
                                nullptr, scratch, 0.0, kStoreAcc, nullptr, s));
         } else {
             NB_HIP(launch_vjp(t, pos_w, mass_w, scratch, 1.0, n, G, part, s));

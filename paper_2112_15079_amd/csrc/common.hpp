@@ -50,6 +50,8 @@ bool tile_supported(const Tile& t);
 int64_t chunk_length(int64_t n, const Tile& t);
 // Chunks actually used for n bodies (<= t.chunks).
 int effective_chunks(int64_t n, const Tile& t);
+// Partials of each body that launch_force writes.
+int force_slots(int precision, int64_t n, const Tile& t);
 
 // ----- force pass (Eq. (1)) ------------------------------------------------
 // part[c*3n + k*n + p] receives the chunk-c partial of component k of a_p.
@@ -86,6 +88,8 @@ int mutual_ranges(int64_t n);
 // Partial slots of a single system's pass: the ranges, plus the extra slots
 // of the split last round (shape (4, 4) only).
 int mutual_slots(int64_t n, int tpl, int waves);
+// The partials of its force pass on a single system (a small FP64 pass has more).
+int mutual_force_slots(int precision, int64_t n, int tpl, int waves);
 // Largest single system the each-pair-once passes take (one partial slot per
 // range of 256 bodies: 512 at the largest).
 constexpr int64_t kMutualMaxN = 131072;

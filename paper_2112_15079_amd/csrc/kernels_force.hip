@@ -667,6 +667,12 @@ int effective_chunks(int64_t n, const Tile& t)
     return (int)((n + L - 1) / L);
 }
 
+int force_slots(int precision, int64_t n, const Tile& t)
+{
+    return t.variant == 5 ? mutual_force_slots(precision, n, t.tpl, t.waves)
+                          : effective_chunks(n, t);
+}
+
 hipError_t launch_force(int precision, const Tile& tile, const double* pos, const double* mass,
                         const double* gm, int64_t n, const int64_t* nmaj, double G, double* part,
                         hipStream_t s)

@@ -348,12 +348,12 @@ __device__ __forceinline__ void tile_sweep(const double* __restrict__ sx,
                                            double* __restrict__ ra, int lane,
                                            const Body (&tg)[KMT], double (&ax)[KMT],
                                            double (&ay)[KMT], double (&az)[KMT],
-                                           const PolyConst& c)
+                                           const PolyConst& c, int q0 = Q0, int q1 = Q1)
 {
     constexpr bool kReact = NSYM > 0;
     const int row = lane >> 4;
     const int col = lane & 15;
-    for (int q = Q0; q < Q1; ++q) {
+    for (int q = q0; q < q1; ++q) {
         const int grp = (row + q) & 3;
         const int home = 16 * grp + col;     // the source this lane starts (and ends) with
         double rx = 0.0, ry = 0.0, rz = 0.0;
@@ -415,18 +415,19 @@ __device__ __forceinline__ void sweep_dispatch(int d, const double* px, const do
                                                const double* pz, const double* pg, double* ra,
                                                int lane, const Body (&tg)[KMT],
                                                double (&ax)[KMT], double (&ay)[KMT],
-                                               double (&az)[KMT], const PolyConst& c)
+                                               double (&az)[KMT], const PolyConst& c, int q0 = 0,
+                                               int q1 = 4)
 {
     // d = J - I0: targets I0 + t < J for t < d, I0 + d == J
     if (d >= KMT) {
-        tile_sweep<KMT, KMT, false>(px, py, pz, pg, ra, lane, tg, ax, ay, az, c);
+        tile_sweep<KMT, KMT, false>(px, py, pz, pg, ra, lane, tg, ax, ay, az, c, q0, q1);
         return;
     }
     switch (d) {
-    case 0: tile_sweep<KMT, 0, true>(px, py, pz, pg, ra, lane, tg, ax, ay, az, c); break;
-    case 1: tile_sweep<KMT, (KMT > 1 ? 1 : 0), true>(px, py, pz, pg, ra, lane, tg, ax, ay, az, c); break;
-    case 2: tile_sweep<KMT, (KMT > 2 ? 2 : 0), true>(px, py, pz, pg, ra, lane, tg, ax, ay, az, c); break;
-    case 3: tile_sweep<KMT, (KMT > 3 ? 3 : 0), true>(px, py, pz, pg, ra, lane, tg, ax, ay, az, c); break;
+    case 0: tile_sweep<KMT, 0, true>(px, py, pz, pg, ra, lane, tg, ax, ay, az, c, q0, q1); break;
+    case 1: tile_sweep<KMT, (KMT > 1 ? 1 : 0), true>(px, py, pz, pg, ra, lane, tg, ax, ay, az, c, q0, q1); break;
+    case 2: tile_sweep<KMT, (KMT > 2 ? 2 : 0), true>(px, py, pz, pg, ra, lane, tg, ax, ay, az, c, q0, q1); break;
+    case 3: tile_sweep<KMT, (KMT > 3 ? 3 : 0), true>(px, py, pz, pg, ra, lane, tg, ax, ay, az, c, q0, q1); break;
     default: break;
     }
 }
@@ -952,6 +953,120 @@ __global__ __launch_bounds__(64 * KMW) void k_force_mutual(const double* __restr
                                 xslot);
 }
 
+// A small FP64 pass, every pair (the diagonal ones too) as four workgroups of
+// the whole pair's wave layout, workgroup h over sub-phase h.  A whole pair's
+// sweep takes 14 us however few there are (one wave per SIMD, each a serial
+// chain of 64 steps), a quarter's 3.5, and three of them fit beside each other on a
+// CU: up to 192 pairs a step takes 18.1 us where it took 20.9 (4,096 and 4,500
+// bodies), 19.7 where it took 21.0 (4,800).  (Four to a CU: 21.7 against 21.1 at
+// 5,000; halves, of which a CU then gets two: 20.8.)
+// Workgroups 0 .. 4 R - 1 run the diagonals, the others go along the
+// super-diagonals (wrapped past range R - 1).  A body of range X meets every
+// range Y in each sub-phase, whose sum (or reaction) goes to slot h R + Y.
+constexpr int kQuarters = 4;
+__global__ __launch_bounds__(256) void k_force_mutual_quarters(const double* __restrict__ pos,
+                                                               const double* __restrict__ gm,
+                                                               int64_t n, int R,
+                                                               double* __restrict__ part)
+{
+    constexpr int T = kMM;
+    __shared__ double src[kMM][kSrcBlock];
+    __shared__ double racc[kMM][3][64];
+    __shared__ double cbuf[(kMM - 1) * T * 3 * 64];   // staged targets, then the waves' sums
+    const int lane = threadIdx.x & 63;
+    const int w = threadIdx.x >> 6;
+    const int h = (int)blockIdx.x % kQuarters;
+    int g = (int)blockIdx.x / kQuarters, r = g;
+    if (g >= R) {
+        const int u = g - R;
+        const int a = u % R;
+        const int b = (a + u / R + 1) % R;
+        g = a < b ? a : b;
+        r = a < b ? b : a;
+    }
+    const int nb = (int)((n + 63) / 64);
+    const int I0 = g * kMM;
+    const int J = r * kMM + w;
+    const int64_t plane = 3 * n;
+
+    double (*tst)[4][64] = reinterpret_cast<double (*)[4][64]>(cbuf);
+    {
+        const Body a = load_body(pos, gm, n, n, (int64_t)(I0 + w) * 64 + lane);
+        const Body b = load_body(pos, gm, n, n, (int64_t)J * 64 + lane);
+        tst[w][0][lane] = a.x;
+        tst[w][1][lane] = a.y;
+        tst[w][2][lane] = a.z;
+        tst[w][3][lane] = a.gm;
+        stage_source(src[w], lane, b);
+        racc[w][0][lane] = 0.0;
+        racc[w][1][lane] = 0.0;
+        racc[w][2][lane] = 0.0;
+    }
+    __syncthreads();
+    NB_MUTUAL_MARK(1);
+    Body tg[T];
+    double ax[T], ay[T], az[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        tg[t] = Body{tst[t][0][lane], tst[t][1][lane], tst[t][2][lane], tst[t][3][lane]};
+        ax[t] = 0.0;
+        ay[t] = 0.0;
+        az[t] = 0.0;
+    }
+    if (J < nb) {
+        const double* sb = src[w];
+        sweep_dispatch<T>(J - I0, sb, sb + 32, sb + 64, sb + 96, &racc[w][0][0], lane, tg, ax, ay,
+                          az, PolyConst{vreg_const(1.875), vreg_const(1.5)}, h, h + 1);
+    }
+    NB_MUTUAL_MARK(2);
+    // the four waves' target sums, each wave adding up one target block in wave
+    // order (the buffer held the staged targets, read before this barrier)
+    __syncthreads();
+    double (*comb)[T - 1][3][64] = reinterpret_cast<double (*)[T - 1][3][64]>(cbuf);
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        if (t == w) continue;
+        const int k = w < t ? w : w - 1;
+        comb[t][k][0][lane] = ax[t];
+        comb[t][k][1][lane] = ay[t];
+        comb[t][k][2][lane] = az[t];
+    }
+    __syncthreads();
+    double sx = 0.0, sy = 0.0, sz = 0.0;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        if (t != w) continue;
+        sx = ax[t];
+        sy = ay[t];
+        sz = az[t];
+    }
+#pragma unroll
+    for (int k = 0; k < T - 1; ++k) {
+        sx += comb[w][k][0][lane];
+        sy += comb[w][k][1][lane];
+        sz += comb[w][k][2][lane];
+    }
+    if (r == g) {   // targets and sources are the same blocks
+        sx += racc[w][0][lane];
+        sy += racc[w][1][lane];
+        sz += racc[w][2][lane];
+    }
+    const int64_t i = (int64_t)(I0 + w) * 64 + lane;
+    if (i < n) {
+        double* pt = part + (int64_t)(h * R + r) * plane;
+        __builtin_nontemporal_store(sx, &pt[i]);
+        __builtin_nontemporal_store(sy, &pt[n + i]);
+        __builtin_nontemporal_store(sz, &pt[2 * n + i]);
+    }
+    const int64_t j = (int64_t)J * 64 + lane;
+    if (r > g && j < n) {
+        double* ps = part + (int64_t)(h * R + g) * plane;
+        __builtin_nontemporal_store(racc[w][0][lane], &ps[j]);
+        __builtin_nontemporal_store(racc[w][1][lane], &ps[n + j]);
+        __builtin_nontemporal_store(racc[w][2][lane], &ps[2 * n + j]);
+    }
+}
+
 // The ensemble: one workgroup per unit (system, g = tblock, r = chunk) of the
 // work list; the partial planes span all systems (stride n_total).
 template <int KMT, int KMW, int PREC>
@@ -1322,6 +1437,21 @@ int mutual_slots(int64_t n, int tpl, int waves)
     return t.R + 2 * t.D;
 }
 
+// Whether the force pass runs its pairs as quarters (k_force_mutual_quarters):
+// as long as they are at most three to a CU.
+static bool mutual_quarters(int precision, int64_t n, int tpl, int waves)
+{
+    const int64_t R = mutual_ranges(n);
+    return precision == 0 && tpl == 4 && waves == 4 &&
+           kQuarters * (R * (R + 1) / 2) <= 3 * kMutualCUs;
+}
+
+int mutual_force_slots(int precision, int64_t n, int tpl, int waves)
+{
+    return mutual_quarters(precision, n, tpl, waves) ? kQuarters * mutual_ranges(n)
+                                                     : mutual_slots(n, tpl, waves);
+}
+
 bool mutual_shape_supported(int tpl, int waves)
 {
     return (tpl == 1 && waves == 4) || (tpl == 2 && waves == 2) || (tpl == 2 && waves == 4) ||
@@ -1417,6 +1547,11 @@ hipError_t launch_force_mutual(int precision, int tpl, int waves, const double* 
         return hipErrorInvalidValue;
     const MutualTail tl = mutual_tail(n, tpl, waves);
     const int64_t pairs = (int64_t)tl.R * (tl.R + 1) / 2;
+    if (mutual_quarters(precision, n, tpl, waves)) {
+        hipLaunchKernelGGL(k_force_mutual_quarters, dim3((unsigned)(kQuarters * pairs)), dim3(256),
+                           0, s, pos, gm, n, tl.R, part);
+        return hipGetLastError();
+    }
     const dim3 grid((unsigned)(tl.F + 2 * (pairs - tl.F)));   // whole pairs, then halves
     if (precision == 0)
         launch_mutual_shape<0>(tpl, waves, grid, pos, gm, n, nullptr, tl, part, s);
