@@ -303,32 +303,40 @@ int group_run(int prec, const double* pos_in, double* pos_out, double* vel, cons
 // caller's stream, two for the adjoint's second, two for its reverse sweep).
 uint32_t* group_reg(uint32_t* flags) { return flags + 16; }
 
-// The shape of the reverse sweep for n bodies.  Up to 2,048 the positions are
-// held in LDS beside the cotangents (us per position at 131, 1,000 and 2,000
-// bodies: 2.9, 5.0 and 10.0, against 3.7, 5.6 and 10.5 read from the caches);
-// beyond them 512 threads with three to five targets each read them ahead
-// (12.0 against 14.3 at 2,079), where registers do not allow more threads.
-GroupVjpShape group_vjp_shape(int64_t n)
+// The shape of the reverse sweep for n bodies (false: none).  A CU must have
+// registers and LDS for a workgroup of it beside one of the run kernel, so that
+// the sweep of a segment and the recompute of the next one run side by side (us
+// per step of the reverse half over 20 segments, side by side, in turn, and by a
+// product and its reduction per position with a recompute by launches: 2.5, 4.1 and
+// 9.6 at 131 bodies, 6.5, 7.9 and 12.9 at 1,000, 12.7, 15.6 and 16.2 at 2,048,
+// 15.2, 18.8 and 16.2 at 2,079; in turn at 2,500 and 3,072: 21.8 and 27.6 against
+// 20.7 and 25.5).  That takes 512 threads, the registers of the shape table, and
+// the LDS up to 2,251 bodies; up to 1,670 there is room for the positions too
+// (1,600 bodies: 9.8 with them in LDS, 10.2 read ahead from the caches).
+bool group_vjp_shape(int64_t n, GroupVjpShape* shape)
 {
-    if (n <= 256) return {1, 8, 512, true};
-    if (n <= 1024) return {1, 4, 1024, true};
-    if (n <= 1280) return {1, 5, 1024, true};
-    if (n <= 1536) return {2, 3, 1024, true};
-    if (n <= 2048) return {2, 4, 1024, true};
-    if (n <= 2560) return {5, 2, 512, false};
-    if (n <= 3072) return {3, 4, 512, false};
-    return {4, 4, 512, false};
+    constexpr size_t kLds = 160 * 1024 - 2048;   // (static LDS and granules)
+    if (n < kGroupMin || n > kGroupMax) return false;
+    const size_t run = group_lds_bytes(n, group_shape(n));
+    auto fits = [&](const GroupVjpShape& g) {
+        *shape = g;
+        return run + group_vjp_lds_bytes(n, g) <= kLds;
+    };
+    if (n <= 256) return fits({1, 8, 512, true});
+    if (n <= 1024) return fits({1, 4, 512, true});
+    if (n <= 1280) return fits({1, 5, 512, true});
+    if (n <= 1536) return fits({2, 3, 512, true});
+    if (n <= 2048) return fits({2, 4, 512, true}) || fits({2, 4, 512, false});
+    return fits({2, 5, 512, false});
 }
 
-// Whether the reverse sweep of segments of K steps takes the group kernel: the
-// sizes of the runs (forward, recompute and sweep, us per step, against the
-// product and its reduction beside the recompute: 6.5 and 14.9 at 131 bodies,
-// 11.8 and 31.6 at 1,000, 28.3 and 33.9 at 2,079, 51 and 58 at 3,500), unless
-// nbody_set_tile chose a tile for the product.  (One position alone would
-// be written where others still read.)
+// Whether the reverse sweep of segments of K steps takes the group kernel, where
+// runs do and unless nbody_set_tile chose a tile for the product.  (One position
+// alone would be written where others still read.)
 bool group_vjp_route(int64_t n, int64_t K)
 {
-    if (n < kGroupMin || n > kGroupMax || K < 2) return false;
+    GroupVjpShape g;
+    if (K < 2 || !group_route(NBODY_FP64, n) || !group_vjp_shape(n, &g)) return false;
     std::lock_guard<std::mutex> lk(g_mu);
     auto it = g_tiles.find(std::make_tuple(1, (int)NBODY_FP64, size_class(n)));
     return it == g_tiles.end() || !it->second.forced;
@@ -338,7 +346,8 @@ bool group_vjp_route(int64_t n, int64_t K)
 // kGroupSegment of them.
 int group_sweep(GroupVjpArgs A, hipStream_t s)
 {
-    const GroupVjpShape g = group_vjp_shape(A.n);
+    GroupVjpShape g;
+    if (!group_vjp_shape(A.n, &g)) return fail(NBODY_EINVAL, "no sweep of %lld bodies", (long long)A.n);
     A.spread = group_spread(A.n);
     int64_t left = A.count;
     for (int64_t pieces = (left + kGroupSegment - 1) / kGroupSegment; pieces > 0; --pieces) {
@@ -1218,6 +1227,11 @@ static int adjoint_core(const double* pos0, const double* vel0, const double* ma
     P.buf[0] = w0;
     P.buf[1] = w1;
     const bool group = group_route(NBODY_FP64, n);
+    // The group kernel's sweep does all positions of a segment in one launch (the
+    // closing half kick too), beside the group kernel's recompute.  A sweep by
+    // launches has a recompute by launches beside it, which leaves it more of
+    // the chip (16.2 against 19.6 us per step at 2,079 bodies).
+    const bool group_rev = group_vjp_route(n, std::min(K, steps));
     const bool small = P.tile.variant == 3;
     const Tile vt = pick_tile(1, NBODY_FP64, n);
     const int vchunks = vjp_chunks(n, vt);
@@ -1242,7 +1256,7 @@ static int adjoint_core(const double* pos0, const double* vel0, const double* ma
     auto maybe_graph = [&](const GraphKey& key, int64_t kseg, auto&& body) -> int {
         return maybe_graph_on(s, key, kseg, body);
     };
-    if (!group) NB_HIP(launch_scale(mass, G, n, gm, s));
+    if (!group_rev) NB_HIP(launch_scale(mass, G, n, gm, s));
     if (forward) {
         NB_HIP(hipMemcpyAsync(ck_r(0), pos0, b3, hipMemcpyDeviceToDevice, s));
         NB_HIP(hipMemcpyAsync(ck_v(0), vel0, b3, hipMemcpyDeviceToDevice, s));
@@ -1282,18 +1296,12 @@ static int adjoint_core(const double* pos0, const double* vel0, const double* ma
     NB_HIP(hipMemcpyAsync(lam_r, grad_posT, b3, hipMemcpyDeviceToDevice, s));
     NB_HIP(hipMemcpyAsync(lam_v, grad_velT, b3, hipMemcpyDeviceToDevice, s));
     NB_HIP(launch_fill(g_m, 0.0, n, s));
-    // The group kernel's sweep does all positions of a segment in one launch (the
-    // closing half kick too).  It holds a workgroup on every CU, as the recompute
-    // does, so the two take turns on the caller's stream (side by side: 12.9
-    // against 12.4 us per step at 1,000 bodies, 29.7 against 28.6 at 2,079).
-    const bool group_rev = group_vjp_route(n, std::min(K, steps));
-    const bool overlap = !group_rev;
     if (steps > 0 && !group_rev) {
         // closing half kick of the last step: v_T = v_{T-1/2} + dt/2 a(r_T)
         NB_HIP(launch_vjp(vt, ck_r(nck), mass, lam_v, 0.5 * dt, n, G, part, s));
         NB_HIP(launch_vjp_reduce(part, vchunks, n, lam_r, g_m, lam_v, dt, true, s));
     }
-    // Segments in reverse order, pipelined over two streams (overlap): the side stream
+    // Segments in reverse order, pipelined over two streams: the side stream
     // recomputes the positions of segment c - 1 (from its checkpoint, into the
     // other segment buffer, with its own partials and velocity) while the
     // caller's stream runs the reverse sweep of segment c.  Events order a
@@ -1304,20 +1312,20 @@ static int adjoint_core(const double* pos0, const double* vel0, const double* ma
     R.part = part2;
     double* segbuf[2] = {seg, seg2};
     bool freed_recorded[2] = {false, false};
-    auto recompute = [&](int64_t c, hipStream_t rs) -> int {
+    auto recompute = [&](int64_t c) -> int {
         const int b = (int)(c & 1);
         const int64_t kseg = std::min(K, steps - c * K);
         double* sg = segbuf[b];
-        if (overlap && freed_recorded[b]) NB_HIP(hipStreamWaitEvent(rs, side->freed[b], 0));
-        NB_HIP(hipMemcpyAsync(sg, ck_r(c), b3, hipMemcpyDeviceToDevice, rs));
-        NB_HIP(hipMemcpyAsync(vtmp2, ck_v(c), b3, hipMemcpyDeviceToDevice, rs));
-        if (group) {
+        if (freed_recorded[b]) NB_HIP(hipStreamWaitEvent(sb, side->freed[b], 0));
+        NB_HIP(hipMemcpyAsync(sg, ck_r(c), b3, hipMemcpyDeviceToDevice, sb));
+        NB_HIP(hipMemcpyAsync(vtmp2, ck_v(c), b3, hipMemcpyDeviceToDevice, sb));
+        if (group_rev) {
             // (the segment's positions r_{cK+1} .. r_{cK+kseg-1}, as below)
             if (kseg >= 2)
                 NB_TRY(group_run(0, sg, nullptr, vtmp2, mass, n, nullptr, G, dt, kseg - 2,
                                       kseg, nullptr, sg + 3 * n, part2, group_reg(flags) + 2,
-                                      flags, rs));
-        } else NB_TRY(maybe_graph_on(rs, key_of(3, kseg, 0, sg), kseg, [&](hipStream_t cs) -> int {
+                                      flags, sb));
+        } else NB_TRY(maybe_graph_on(sb, key_of(3, kseg, 0, sg), kseg, [&](hipStream_t cs) -> int {
             // positions r_{cK+1} .. r_{cK+kseg-1} of the segment into its slots
             if (small && kseg >= 2)
                 NB_HIP(launch_run_small(0, R.tile, sg, nullptr, vtmp2, mass, n, nullptr, G, dt, 0,
@@ -1328,14 +1336,14 @@ static int adjoint_core(const double* pos0, const double* vel0, const double* ma
             }
             return (int)NBODY_OK;
         }));
-        if (overlap) NB_HIP(hipEventRecord(side->ready[b], rs));
+        NB_HIP(hipEventRecord(side->ready[b], sb));
         return NBODY_OK;
     };
     auto sweep = [&](int64_t c) -> int {
         const int b = (int)(c & 1);
         const int64_t kseg = std::min(K, steps - c * K);
         const double* sg = segbuf[b];
-        if (overlap) NB_HIP(hipStreamWaitEvent(s, side->ready[b], 0));
+        NB_HIP(hipStreamWaitEvent(s, side->ready[b], 0));
         if (group_rev) {   // (two positions at least: K of them, or one and the last)
             GroupVjpArgs A{};
             A.seg = sg;
@@ -1364,22 +1372,17 @@ static int adjoint_core(const double* pos0, const double* vel0, const double* ma
             }
             return (int)NBODY_OK;
         }));
-        if (overlap) NB_HIP(hipEventRecord(side->freed[b], s));
+        NB_HIP(hipEventRecord(side->freed[b], s));
         freed_recorded[b] = true;
         return NBODY_OK;
     };
-    if (!overlap) {
-        for (int64_t c = nck - 1; c >= 0; --c) {
-            NB_TRY(recompute(c, s));
-            NB_TRY(sweep(c));
-        }
-    } else if (nck > 0) {
+    if (nck > 0) {
         // the checkpoints (forward run, above) and G m come before any recompute
         NB_HIP(hipEventRecord(side->fwd, s));
         NB_HIP(hipStreamWaitEvent(sb, side->fwd, 0));
-        NB_TRY(recompute(nck - 1, sb));
+        NB_TRY(recompute(nck - 1));
         for (int64_t c = nck - 1; c >= 0; --c) {
-            if (c > 0) NB_TRY(recompute(c - 1, sb));
+            if (c > 0) NB_TRY(recompute(c - 1));
             NB_TRY(sweep(c));
         }
     }

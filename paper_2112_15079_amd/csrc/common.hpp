@@ -191,9 +191,11 @@ struct GroupVjpShape {
     int tpl, lanes, threads;
     bool held;
 };
+// (the last entry: wavefronts per SIMD that its registers must allow)
 #define NB_GROUP_VJP_SHAPES(X)                                                         \
-    X(1, 8, 512, true) X(1, 4, 1024, true) X(2, 4, 1024, true) X(5, 2, 512, false)     \
-    X(3, 4, 512, false) X(4, 4, 512, false) X(1, 5, 1024, true) X(2, 3, 1024, true)
+    X(1, 8, 512, true, 1) X(1, 4, 512, true, 6) X(1, 5, 512, true, 6)                  \
+    X(2, 3, 512, true, 4) X(2, 4, 512, true, 4) X(2, 4, 512, false, 3)                 \
+    X(2, 5, 512, false, 4)
 size_t group_vjp_lds_bytes(int64_t n, const GroupVjpShape& g);
 hipError_t launch_group_vjp(const GroupVjpShape& g, const GroupVjpArgs& A, hipStream_t s);
 

@@ -518,14 +518,16 @@ __global__ __launch_bounds__(NT) void k_group(GroupArgs A)
 // positions, last to first, lam_r += c J^T lam_v and g_m += c M^T lam_v, then
 // (but at the run's first) lam_v += dt lam_r.  A product and its reduction per
 // position are bound by two kernel boundaries and the partials' round trip:
-// 9.5, 16 and 19 us at 131, 1,000 and 2,079 bodies, with the recompute beside
-// them; here 2.9, 5.0 and 12, of which 0.1, 1.3 and 6 are arithmetic.  The
+// 9.6, 12.9 and 16.2 us a step at 131, 1,000 and 2,079 bodies, with the recompute
+// beside them; here 2.5, 6.5 and 15.2, with a run kernel's recompute on the
+// same CUs, of which the arithmetic of both is 0.1, 1.8 and 9.  The
 // exchange is the one above with lam_v (and the mass) in the place of the
 // position (and G m); the positions are known beforehand, so they are staged
 // ahead of the exchange: into LDS (HELD), or by each lane into registers, P
-// rounds at a time, where LDS does not hold both.
-template <int T, int TT, int NT, bool HELD>
-__global__ __launch_bounds__(NT) void k_group_vjp(GroupVjpArgs A)
+// rounds at a time, where LDS does not hold both.  MW: wavefronts per SIMD whose
+// registers the kernel may not exceed, so that a run kernel's fit beside it.
+template <int T, int TT, int NT, bool HELD, int MW>
+__global__ __launch_bounds__(NT, MW) void k_group_vjp(GroupVjpArgs A)
 {
     using D = GroupDims<T, TT, NT>;
     constexpr int S = D::S;
@@ -738,14 +740,14 @@ hipError_t launch_shape(const GroupArgs& A, int blocks, size_t lds, hipStream_t 
     return hipGetLastError();
 }
 
-template <int T, int TT, int NT, bool HELD>
+template <int T, int TT, int NT, bool HELD, int MW>
 hipError_t launch_vjp_shape(const GroupVjpArgs& A, int blocks, size_t lds, hipStream_t s)
 {
     static std::atomic<uint64_t> allowed{0};
     const hipError_t e =
-        allow_lds(reinterpret_cast<const void*>(&k_group_vjp<T, TT, NT, HELD>), allowed);
+        allow_lds(reinterpret_cast<const void*>(&k_group_vjp<T, TT, NT, HELD, MW>), allowed);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_group_vjp<T, TT, NT, HELD>), dim3((unsigned)(blocks * A.spread)), dim3(NT), lds,
+    hipLaunchKernelGGL((k_group_vjp<T, TT, NT, HELD, MW>), dim3((unsigned)(blocks * A.spread)), dim3(NT), lds,
                        s, A);
     return hipGetLastError();
 }
@@ -800,9 +802,9 @@ hipError_t launch_group_vjp(const GroupVjpShape& g, const GroupVjpArgs& A, hipSt
     if (e != hipSuccess) return e;
     const int64_t tw = (int64_t)g.tpl * g.lanes;
     const int blocks = (int)((A.n + tw - 1) / tw);
-#define NB_CASE(TT_, LL, NN, HH)                                                 \
+#define NB_CASE(TT_, LL, NN, HH, MW)                                              \
     if (g.tpl == TT_ && g.lanes == LL && g.threads == NN && g.held == HH)        \
-        return launch_vjp_shape<TT_, LL, NN, HH>(A, blocks, lds, s);
+        return launch_vjp_shape<TT_, LL, NN, HH, MW>(A, blocks, lds, s);
     NB_GROUP_VJP_SHAPES(NB_CASE)
 #undef NB_CASE
     return hipErrorInvalidValue;

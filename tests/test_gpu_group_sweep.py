@@ -55,3 +55,30 @@ def test_sweep_matches_one_product_per_position(n, steps, K):
 @pytest.mark.parametrize("n", [1280, 1281, 1536, 1537])
 def test_sweep_with_three_and_five_lanes_side_by_side(n):
     test_sweep_matches_one_product_per_position(n, 7, 3)
+
+
+@pytest.mark.parametrize("n", [1670, 1671, 2079, 2251, 2252])
+@pytest.mark.parametrize("steps,K", [(11, 2), (13, 4)])
+def test_sweep_beside_the_recompute_of_many_segments(n, steps, K):
+    test_sweep_matches_one_product_per_position(n, steps, K)
+
+
+def test_two_streams_at_once_equal_one_after_the_other():
+    """Two reverse sweeps in flight, each beside its recompute: whichever workgroups
+    come late, the gradients are the same bit for bit."""
+    n, steps, K = 700, 60, 10
+    s = S.solar_system(5, n - 31)
+    args = [T(s.pos), T(s.vel), T(s.mass), s.G, 0.1, steps, K, T(np.ones((3, n))),
+            T(np.ones((3, n)))]
+    one = [x.clone() for x in nb.verlet_adjoint(*args)]
+    torch.cuda.synchronize()
+    outs = []
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    for _ in range(3):
+        for st in streams:
+            with torch.cuda.stream(st):
+                outs.append(nb.verlet_adjoint(*args))
+    torch.cuda.synchronize()
+    for o in outs:
+        for x, y in zip(one, o):
+            assert torch.equal(x, y)
