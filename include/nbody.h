@@ -222,7 +222,9 @@ int32_t nbody_verlet_adjoint_from_checkpoints(const double* checkpoints, const d
  * concatenated SoA arrays (plane stride = offsets_host[num_systems]); bodies
  * of different systems do not interact.  offsets_host is a HOST array of
  * num_systems + 1 non-decreasing values starting at 0; every system has at
- * least one body.  The step loop is captured into a HIP graph on first use
+ * least one body.  Ensembles of small systems (none above 2,048 bodies, sum
+ * n_k^2 at most 3e8, no tile from nbody_set_tile) run in workgroups that stay on the chip;
+ * otherwise the step loop is captured into a HIP graph on first use
  * and replayed.  Tile: the one nbody_autotune_batched chose, else each pair
  * once (variant 5, (4, 4)) when every system has at most 10,240 bodies and
  * sum n_k^2 / sum n_k >= 2,048, else the one-way heuristic; a variant-5 tile
@@ -278,10 +280,20 @@ int32_t nbody_get_flags(void* workspace, void* stream, int32_t clear, int32_t* f
  * whole round of 256 workgroups are few (at most 128, of at most 16,384
  * pairs), each of them runs as two workgroups over half of the sub-phases
  * each, and extra slots take the second halves' target sums and reactions
- * (47 slots at n = 10,425); the transpose-Jacobian pass (kind 1, variant 5,
- * shape (4, 4)) splits its last round the same way.  Results stay bitwise
+ * (47 slots at n = 10,425); an FP64 force pass of at most 192 range pairs
+ * (n <= 4,864) runs each of them as four, with four slots per range.  The
+ * transpose-Jacobian pass (kind 1, variant 5, shape (4, 4)) splits its last
+ * round into halves the same way.  Results stay bitwise
  * repeatable.  The heuristic picks (4, 4) from n = 4,096 (FP64) or 8,000
- * (split) up to n = 131,072, and for kind 1 from n = 4,500. */
+ * (split) up to n = 131,072, and for kind 1 from n = 4,500.
+ *
+ * From n = 80 to 4,095 (FP64 and split) a force evaluation or a run whose size
+ * class has no tile from nbody_set_tile takes none of these: at most 256 workgroups
+ * stay on the chip for all steps, own a few targets each and exchange
+ * positions.  The adjoint's forward run does so too, and up to n = 2,251 its
+ * recompute and its reverse sweep (kind 1, likewise without a tile set).
+ * nbody_get_tile, nbody_autotune and nbody_time_force report and time the tiles
+ * above; runs take a tile at these sizes when nbody_set_tile sets it. */
 typedef struct {
     int32_t targets_per_lane;
     int32_t waves;
