@@ -107,7 +107,8 @@ size_t nbody_workspace_bytes(int32_t op, int64_t n_total, int32_t num_systems,
 /* Eq. (1): acc_out[3n] = accelerations of all n bodies at positions pos.
  * vel, dt and steps are accepted for a uniform argument block and ignored
  * (vel may be NULL).  precision: nbody_precision; small_mass is the split
- * threshold in mass units (ignored for NBODY_FP64).  n >= 1. */
+ * threshold in mass units (ignored for NBODY_FP64).  n >= 1.  acc_out may
+ * overlap pos and mass (a stage buffer overwritten by its acceleration). */
 int32_t nbody_accel(const double* pos, const double* vel, const double* mass,
                     int64_t n, double G, double dt, int64_t steps,
                     double* acc_out, int32_t precision, double small_mass,

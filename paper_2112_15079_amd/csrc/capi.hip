@@ -8,6 +8,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -769,6 +770,12 @@ int split_prepare(void* ws, const Layout& L, const double* pos, const double* ve
     return NBODY_OK;
 }
 
+// Whether two arrays of doubles share memory.
+bool overlap(const double* a, int64_t na, const double* b, int64_t nb)
+{
+    return std::less<const double*>()(a, b + nb) && std::less<const double*>()(b, a + na);
+}
+
 // Fourth-order Runge-Kutta: `steps` steps of four force passes and stage
 // updates; the position buffer r is updated in place.  Groups of kRk4Graph
 // steps are replayed from a captured graph.
@@ -852,21 +859,28 @@ int32_t nbody_accel(const double* pos, const double* vel, const double* mass, in
     const bool group = group_route(precision, n);
     const bool small = tile.variant == 3;
     const bool fused = tile.variant == 4;
-    if (precision == NBODY_FP64) {
-        if (group)
-            return group_run(0, pos, nullptr, nullptr, mass, n, nullptr, G, 0.0, 0, 0, acc_out,
-                             nullptr, nullptr, nullptr, flags, s);
-        if (small) {
+    if (precision == NBODY_FP64 && (group || small || fused)) {
+        // One kernel reads the bodies and stores the accelerations: where those
+        // go over its inputs, by way of the workspace (a workgroup that starts
+        // late still reads what another has long stored).
+        const bool over = overlap(acc_out, 3 * n, pos, 3 * n) || overlap(acc_out, 3 * n, mass, n);
+        double* acc = over ? at<double>(workspace, L.alt) : acc_out;
+        if (group) {
+            NB_TRY(group_run(0, pos, nullptr, nullptr, mass, n, nullptr, G, 0.0, 0, 0, acc,
+                             nullptr, nullptr, nullptr, flags, s));
+        } else if (small) {
             NB_HIP(launch_run_small(0, tile, pos, nullptr, nullptr, mass, n, nullptr, G, 0.0, 0, 0,
-                                    0, acc_out, nullptr, flags, s));
-            return NBODY_OK;
-        }
-        NB_HIP(launch_scale(mass, G, n, gm, s));
-        if (fused) {
+                                    0, acc, nullptr, flags, s));
+        } else {
+            NB_HIP(launch_scale(mass, G, n, gm, s));
             NB_HIP(launch_step_fused(0, tile, pos, nullptr, nullptr, gm, n, nullptr, 0.0, kStoreAcc,
-                                     acc_out, flags, s));
-            return NBODY_OK;
+                                     acc, flags, s));
         }
+        if (over) NB_HIP(launch_scale(acc, 1.0, 3 * n, acc_out, s));
+        return NBODY_OK;
+    }
+    if (precision == NBODY_FP64) {
+        NB_HIP(launch_scale(mass, G, n, gm, s));
         NB_HIP(launch_force(0, tile, pos, mass, gm, n, nullptr, G, part, s));
         NB_HIP(launch_step(part, chunks, nullptr, n, nullptr, nullptr, nullptr, acc_out, 0.0,
                            kStoreAcc, flags, s));
