@@ -291,8 +291,8 @@ int32_t nbody_get_flags(void* workspace, void* stream, int32_t clear, int32_t* f
  * From n = 80 to 4,095 (FP64 and split) a force evaluation or a run whose size
  * class has no tile from nbody_set_tile takes none of these: at most 256 workgroups
  * stay on the chip for all steps, own a few targets each and exchange
- * positions.  The adjoint's forward run does so too, and up to n = 2,251 its
- * recompute and its reverse sweep (kind 1, likewise without a tile set).
+ * positions.  The adjoint's forward run and its recompute do so too, and its
+ * reverse sweep (kind 1, likewise without a tile set).
  * nbody_get_tile, nbody_autotune and nbody_time_force report and time the tiles
  * above; runs take a tile at these sizes when nbody_set_tile sets it. */
 typedef struct {

@@ -304,40 +304,44 @@ int group_run(int prec, const double* pos_in, double* pos_out, double* vel, cons
 // caller's stream, two for the adjoint's second, two for its reverse sweep).
 uint32_t* group_reg(uint32_t* flags) { return flags + 16; }
 
-// The shape of the reverse sweep for n bodies (false: none).  A CU must have
-// registers and LDS for a workgroup of it beside one of the run kernel, so that
-// the sweep of a segment and the recompute of the next one run side by side (us
-// per step of the reverse half over 20 segments, side by side, in turn, and by a
-// product and its reduction per position with a recompute by launches: 2.5, 4.1 and
-// 9.6 at 131 bodies, 6.5, 7.9 and 12.9 at 1,000, 12.7, 15.6 and 16.2 at 2,048,
-// 15.2, 18.8 and 16.2 at 2,079; in turn at 2,500 and 3,072: 21.8 and 27.6 against
-// 20.7 and 25.5).  That takes 512 threads, the registers of the shape table, and
-// the LDS up to 2,251 bodies; up to 1,670 there is room for the positions too
-// (1,600 bodies: 9.8 with them in LDS, 10.2 read ahead from the caches).
-bool group_vjp_shape(int64_t n, GroupVjpShape* shape)
+// The shape of the reverse sweep for n bodies, and whether a CU has registers and
+// LDS for a workgroup of it beside one of the run kernel, so that the sweep of a
+// segment and the recompute of the next one run side by side (us per step of the
+// reverse half over 20 segments, side by side, in turn, and by a product and its
+// reduction per position with a recompute by launches: 2.5, 4.1 and 9.6 at 131
+// bodies, 6.5, 7.9 and 12.9 at 1,000, 12.7, 15.6 and 16.2 at 2,048, 15.2, 18.8
+// and 16.2 at 2,079).  That takes 512 threads, the registers of the shape table,
+// and the LDS up to 2,251 bodies; up to 1,670 there is room for the positions
+// too (1,600 bodies: 9.8 with them in LDS, 10.2 read ahead from the caches).
+// Above, the two take turns, in shapes that have a CU to themselves (forward,
+// recompute and sweep, in turn against all three by launches: over two segments
+// 29.0 and 41.6 at 2,252, 39.1 and 51.5 at 3,072, 59.1 and 69.4 at 4,095; over 20
+// segments, where launches overlap better, 30.6 and 37.2, 40.4 and 45.2, 60.6 and
+// 64.7, at 3,073 48.6 and 47.3).
+GroupVjpShape group_vjp_shape(int64_t n, bool* beside)
 {
     constexpr size_t kLds = 160 * 1024 - 2048;   // (static LDS and granules)
-    if (n < kGroupMin || n > kGroupMax) return false;
     const size_t run = group_lds_bytes(n, group_shape(n));
-    auto fits = [&](const GroupVjpShape& g) {
-        *shape = g;
-        return run + group_vjp_lds_bytes(n, g) <= kLds;
-    };
-    if (n <= 256) return fits({1, 8, 512, true});
-    if (n <= 1024) return fits({1, 4, 512, true});
-    if (n <= 1280) return fits({1, 5, 512, true});
-    if (n <= 1536) return fits({2, 3, 512, true});
-    if (n <= 2048) return fits({2, 4, 512, true}) || fits({2, 4, 512, false});
-    return fits({2, 5, 512, false});
+    auto fits = [&](const GroupVjpShape& g) { return run + group_vjp_lds_bytes(n, g) <= kLds; };
+    *beside = true;
+    if (n <= 256) return {1, 8, 512, true};
+    if (n <= 1024) return {1, 4, 512, true};
+    if (n <= 1280) return {1, 5, 512, true};
+    if (n <= 1536) return {2, 3, 512, true};
+    if (n <= 2048) return {2, 4, 512, fits({2, 4, 512, true})};
+    if (fits({2, 5, 512, false})) return {2, 5, 512, false};
+    *beside = false;
+    if (n <= 2560) return {5, 2, 512, false};
+    if (n <= 3072) return {3, 4, 512, false};
+    return {4, 4, 512, false};
 }
 
 // Whether the reverse sweep of segments of K steps takes the group kernel, where
-// runs do and unless nbody_set_tile chose a tile for the product.  (One position
-// alone would be written where others still read.)
-bool group_vjp_route(int64_t n, int64_t K)
+// the runs do (`group`) and unless nbody_set_tile chose a tile for the product.
+// (One position alone would be written where others still read.)
+bool group_vjp_route(bool group, int64_t n, int64_t K)
 {
-    GroupVjpShape g;
-    if (K < 2 || !group_route(NBODY_FP64, n) || !group_vjp_shape(n, &g)) return false;
+    if (K < 2 || !group) return false;
     std::lock_guard<std::mutex> lk(g_mu);
     auto it = g_tiles.find(std::make_tuple(1, (int)NBODY_FP64, size_class(n)));
     return it == g_tiles.end() || !it->second.forced;
@@ -347,8 +351,8 @@ bool group_vjp_route(int64_t n, int64_t K)
 // kGroupSegment of them.
 int group_sweep(GroupVjpArgs A, hipStream_t s)
 {
-    GroupVjpShape g;
-    if (!group_vjp_shape(A.n, &g)) return fail(NBODY_EINVAL, "no sweep of %lld bodies", (long long)A.n);
+    bool beside;
+    const GroupVjpShape g = group_vjp_shape(A.n, &beside);
     A.spread = group_spread(A.n);
     int64_t left = A.count;
     for (int64_t pieces = (left + kGroupSegment - 1) / kGroupSegment; pieces > 0; --pieces) {
@@ -1240,12 +1244,18 @@ static int adjoint_core(const double* pos0, const double* vel0, const double* ma
     P.vel = wv;
     P.buf[0] = w0;
     P.buf[1] = w1;
+    // The recompute takes the forward run's kernel, whichever that is: the sweep
+    // linearises about the very positions of the run, bit for bit.
     const bool group = group_route(NBODY_FP64, n);
     // The group kernel's sweep does all positions of a segment in one launch (the
-    // closing half kick too), beside the group kernel's recompute.  A sweep by
-    // launches has a recompute by launches beside it, which leaves it more of
-    // the chip (16.2 against 19.6 us per step at 2,079 bodies).
-    const bool group_rev = group_vjp_route(n, std::min(K, steps));
+    // closing half kick too), beside the group kernel's recompute or in turn with
+    // it; then the second stream is the caller's.
+    const bool group_rev = group_vjp_route(group, n, std::min(K, steps));
+    if (group_rev) {
+        bool beside;
+        (void)group_vjp_shape(n, &beside);
+        if (!beside) sb = s;
+    }
     const bool small = P.tile.variant == 3;
     const Tile vt = pick_tile(1, NBODY_FP64, n);
     const int vchunks = vjp_chunks(n, vt);
@@ -1270,7 +1280,7 @@ static int adjoint_core(const double* pos0, const double* vel0, const double* ma
     auto maybe_graph = [&](const GraphKey& key, int64_t kseg, auto&& body) -> int {
         return maybe_graph_on(s, key, kseg, body);
     };
-    if (!group_rev) NB_HIP(launch_scale(mass, G, n, gm, s));
+    if (!group) NB_HIP(launch_scale(mass, G, n, gm, s));
     if (forward) {
         NB_HIP(hipMemcpyAsync(ck_r(0), pos0, b3, hipMemcpyDeviceToDevice, s));
         NB_HIP(hipMemcpyAsync(ck_v(0), vel0, b3, hipMemcpyDeviceToDevice, s));
@@ -1333,7 +1343,7 @@ static int adjoint_core(const double* pos0, const double* vel0, const double* ma
         if (freed_recorded[b]) NB_HIP(hipStreamWaitEvent(sb, side->freed[b], 0));
         NB_HIP(hipMemcpyAsync(sg, ck_r(c), b3, hipMemcpyDeviceToDevice, sb));
         NB_HIP(hipMemcpyAsync(vtmp2, ck_v(c), b3, hipMemcpyDeviceToDevice, sb));
-        if (group_rev) {
+        if (group) {
             // (the segment's positions r_{cK+1} .. r_{cK+kseg-1}, as below)
             if (kseg >= 2)
                 NB_TRY(group_run(0, sg, nullptr, vtmp2, mass, n, nullptr, G, dt, kseg - 2,

@@ -195,7 +195,8 @@ struct GroupVjpShape {
 #define NB_GROUP_VJP_SHAPES(X)                                                         \
     X(1, 8, 512, true, 1) X(1, 4, 512, true, 6) X(1, 5, 512, true, 6)                  \
     X(2, 3, 512, true, 4) X(2, 4, 512, true, 4) X(2, 4, 512, false, 3)                 \
-    X(2, 5, 512, false, 4)
+    X(2, 5, 512, false, 4) X(5, 2, 512, false, 2) X(3, 4, 512, false, 2)               \
+    X(4, 4, 512, false, 2)
 size_t group_vjp_lds_bytes(int64_t n, const GroupVjpShape& g);
 hipError_t launch_group_vjp(const GroupVjpShape& g, const GroupVjpArgs& A, hipStream_t s);
 
