@@ -241,8 +241,7 @@ bool group_route(int prec, int64_t n)
     return it == g_tiles.end() || !it->second.forced;
 }
 
-// Launch indices of one launch: as many steps as a run whose registration
-// found part of the workgroups missing goes on with the others' share.
+// Launch indices of one launch.
 constexpr int64_t kGroupSegment = 1024;
 
 // Launch indices 0 .. last of a run by the group kernel: A with everything but
@@ -271,7 +270,7 @@ int group_launches(int prec, const GroupShape& g, GroupArgs A, int blocks, int64
 // pos, vel (with traj the positions after each drift are stored and pos is only
 // read); or, with acc, the accelerations at pos (body p's at acc_perm[p] if
 // given).  xbuf: 12 n doubles, 16-byte
-// aligned; reg: two words (both unused when last = 0).
+// aligned; reg: its registration words (both unused when last = 0).
 int group_run(int prec, const double* pos_in, double* pos_out, double* vel, const double* mass,
               int64_t n, const int64_t* nmaj, double G, double dt, int64_t last, int64_t steps,
               double* acc, double* traj, double* xbuf, uint32_t* reg, uint32_t* flags,
@@ -300,9 +299,12 @@ int group_run(int prec, const double* pos_in, double* pos_out, double* vel, cons
     return group_launches(prec, g, A, (int)((n + tw - 1) / tw), n, 1, last, s);
 }
 
-// The registration words of a workspace: behind the flags word (two for the
-// caller's stream, two for the adjoint's second, two for its reverse sweep).
-uint32_t* group_reg(uint32_t* flags) { return flags + 16; }
+// The registration words of a workspace, behind the flags word: those of the
+// caller's stream (0), the adjoint's second (1) and its reverse sweep (2).
+uint32_t* group_reg(uint32_t* flags, int which = 0)
+{
+    return flags + 16 + kGroupRegWords * which;
+}
 
 // The shape of the reverse sweep for n bodies, and whether a CU has registers and
 // LDS for a workgroup of it beside one of the run kernel, so that the sweep of a
@@ -1347,7 +1349,7 @@ static int adjoint_core(const double* pos0, const double* vel0, const double* ma
             // (the segment's positions r_{cK+1} .. r_{cK+kseg-1}, as below)
             if (kseg >= 2)
                 NB_TRY(group_run(0, sg, nullptr, vtmp2, mass, n, nullptr, G, dt, kseg - 2,
-                                      kseg, nullptr, sg + 3 * n, part2, group_reg(flags) + 2,
+                                      kseg, nullptr, sg + 3 * n, part2, group_reg(flags, 1),
                                       flags, sb));
         } else NB_TRY(maybe_graph_on(sb, key_of(3, kseg, 0, sg), kseg, [&](hipStream_t cs) -> int {
             // positions r_{cK+1} .. r_{cK+kseg-1} of the segment into its slots
@@ -1377,7 +1379,7 @@ static int adjoint_core(const double* pos0, const double* vel0, const double* ma
             A.lam_v = lam_v;
             A.g_m = g_m;
             A.xbuf = part;
-            A.reg = group_reg(flags) + 4;
+            A.reg = group_reg(flags, 2);
             A.n = n;
             A.G = G;
             A.dt = dt;

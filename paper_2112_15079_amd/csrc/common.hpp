@@ -141,13 +141,14 @@ struct GroupUnit {
     int32_t workgroups;
     int32_t rank;       // among the system's workgroups (one-index launches)
 };
+constexpr int kGroupRegWords = 4;   // registration words per system
 struct GroupArgs {
     const double* pos_in;
     double* pos_out;        // may be pos_in when i1 > i0; NULL: not stored
     double* vel;
     const double* mass;
     double* xbuf;           // 12 words per body (i1 > i0), 16-byte aligned
-    uint32_t* reg;          // 2 words per system (i1 > i0)
+    uint32_t* reg;          // kGroupRegWords per system, 8-byte aligned (i1 > i0)
     const GroupUnit* units; // NULL: one system of n bodies
     const int64_t* nmaj;    // split form
     double* acc;            // NULL or a(r)
@@ -179,7 +180,7 @@ struct GroupVjpArgs {
     double* lam_v;
     double* g_m;
     double* xbuf;   // 12 words per body, 16-byte aligned
-    uint32_t* reg;  // 2 words
+    uint32_t* reg;  // kGroupRegWords, 8-byte aligned
     int64_t n;
     double G, dt;
     int64_t k1, count;

@@ -1,6 +1,6 @@
 // Whole runs of the kick-drift-kick loop of Eqs. (3)-(4) in one launch, for
 // systems too large for one workgroup and too small to fill the chip
-// (about 10^2 to 5*10^3 bodies), and for ensembles of such systems.
+// (80 to 4,095 bodies), and for ensembles of such systems.
 //
 // Below a few thousand bodies a force pass is a microsecond or two of
 // arithmetic; a step made of a force kernel and an epilogue is bound by two
@@ -25,12 +25,19 @@
 // complete finds the buffer of r_{i+2} reset.
 //
 // No workgroup waits for one that may not be on the chip.  The workgroups of
-// a system register at entry; the first to arrive closes the registration
-// when all have come, or after kRegisterTicks (other work may hold part of the
-// chip), and those that registered share the virtual groups among
-// themselves.  A workgroup that comes later leaves at once.  So every wait is
-// on a workgroup that is resident, and results do not depend on how many
-// there are: a virtual group's arithmetic is the same whoever runs it.
+// a system register at entry; the first to arrive starts the run when all have
+// come, or after kRegisterTicks (other work may hold part of the chip), and
+// those that registered share the virtual groups among themselves.  A workgroup
+// that comes later joins at the next even launch index: the exchange buffers
+// hold all it needs but the state that only owners keep (velocities; gradients
+// in the sweep), which while workgroups are missing is stored past the caches
+// ahead of the position, and read behind an acquire.  So every wait is on a
+// workgroup that is resident, a run that began on a corner of the chip has all
+// of it soon after other work ends, and results do not depend on how many
+// share the work: a virtual group's arithmetic is the same whoever runs it.
+// (Two runs at once, 1,000 bodies and 1,000 steps each: 7.4 ms, one alone 3.4,
+// and 82 where late workgroups left for the rest of the launch; 4,000 bodies, 500
+// steps: 17, 7.7 and 243.)
 //
 // The pair arithmetic and the two forms are those of the multi-kernel passes:
 // FP64, or (SPLIT, class order) heavy sources with one Newton step and light
@@ -47,15 +54,20 @@ namespace {
 using namespace pm;
 
 constexpr uint64_t kSentinel = 0xFFF4B0D1E5A11CEDull;   // a signalling NaN
-constexpr uint32_t kClosed = 0x80000000u;
-constexpr uint64_t kRegisterTicks = 200000;   // 2 ms of the 100 MHz counter
+constexpr uint64_t kRunEnded = ~(uint64_t)0;
+#ifndef NB_GROUP_REGISTER_TICKS   // (a test instrument sets it, and what follows)
+#define NB_GROUP_REGISTER_TICKS 200000
+#define NB_GROUP_ENTRY(reg)
+#endif
+constexpr uint64_t kRegisterTicks = NB_GROUP_REGISTER_TICKS;   // (2 ms of the 100 MHz counter)
 constexpr int kPollBudget = 1 << 26;          // polls of a thread, a last resort
 constexpr int kMaxLds = 160 * 1024 - 256;     // beside the kernel's static LDS
 constexpr int kBlkG = 16;                     // FP32 block length of the light sums
 
-__device__ __forceinline__ double poll_load(const double* p)
+// A store past the caches that other XCDs' loads do not reach.
+__device__ __forceinline__ void agent_store(double* p, double v)
 {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Two words at word `off` of `base`, with the cache policy of an agent-scope
@@ -116,39 +128,93 @@ __device__ __forceinline__ float light_gm(double slot)
     return __builtin_bit_cast(float, (uint32_t)__builtin_bit_cast(uint64_t, slot));
 }
 
-// Registers the workgroup among the `planned` ones of its system (reg: a count
-// and, once closed, the number that share the work).  False: it came too
-// late and must leave.  Every wait here is on a workgroup that has registered,
-// so it is on the chip, and the first one closes in bounded time.
-__device__ __forceinline__ bool register_workgroup(uint32_t* reg, int planned, int& rank,
-                                                   int& present)
+// A workgroup's place among the `planned` ones of its system.  reg: how many have
+// come, how many the run began with, and a word of 64 bits that says how many
+// share the work and from which launch index on (counted from the launch's first).
+struct Crew {
+    int rank, present;
+    int first;     // the launch index this workgroup begins at
+    int moving;    // the run began without all of them: state changes hands
+};
+
+__device__ __forceinline__ uint64_t* crew_word(uint32_t* reg)
 {
-    __shared__ uint32_t s_rank, s_count;
+    return reinterpret_cast<uint64_t*>(reg + 2);
+}
+
+__device__ __forceinline__ uint64_t load_word(const uint64_t* p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Registers the workgroup.  False: it came too late and must leave.  Every wait
+// here is on the first workgroup, which is on the chip, starts the run in bounded
+// time and, while some are missing, says every second launch index how many
+// share the work from the next on, and at last that the run has ended.  A
+// workgroup that it counts in finds that index here in time: it cannot be
+// overtaken, as the others wait for its positions.
+__device__ __forceinline__ bool register_workgroup(uint32_t* reg, int planned, Crew& crew)
+{
+    __shared__ uint32_t s_crew[3];
+    NB_GROUP_ENTRY(reg)
     if (threadIdx.x == 0) {
         const uint32_t r = __hip_atomic_fetch_add(&reg[0], 1u, __ATOMIC_RELAXED,
                                                   __HIP_MEMORY_SCOPE_AGENT);
-        uint32_t count = 0;
-        if (r == 0) {   // the first: close the registration
+        uint64_t word = 0;
+        if (r == 0) {   // the first: start the run
             const uint64_t t0 = wall_clock64();
-            while (__hip_atomic_load(&reg[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
-                       (uint32_t)planned &&
+            uint32_t count;
+            while ((count = __hip_atomic_load(&reg[0], __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_AGENT)) < (uint32_t)planned &&
                    wall_clock64() - t0 < kRegisterTicks) {
             }
-            count = __hip_atomic_fetch_or(&reg[0], kClosed, __ATOMIC_RELAXED,
-                                          __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&reg[1], count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        } else if (!(r & kClosed)) {
-            while ((count = __hip_atomic_load(&reg[1], __ATOMIC_RELAXED,
-                                              __HIP_MEMORY_SCOPE_AGENT)) == 0) {
+            word = count;
+            reg[1] = count;
+            __hip_atomic_store(crew_word(reg), word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+            while ((uint32_t)(word = load_word(crew_word(reg))) <= r) {
             }
         }
-        s_rank = r;
-        s_count = count;
+        s_crew[0] = r;
+        s_crew[1] = (uint32_t)word;
+        s_crew[2] = (uint32_t)(word >> 32);
     }
     __syncthreads();
-    rank = (int)s_rank;
-    present = (int)s_count;
-    return !(s_rank & kClosed);
+    crew.rank = __builtin_amdgcn_readfirstlane((int)s_crew[0]);
+    crew.present = __builtin_amdgcn_readfirstlane((int)s_crew[1]);
+    crew.first = __builtin_amdgcn_readfirstlane((int)s_crew[2]);
+    crew.moving =
+        __builtin_amdgcn_readfirstlane(crew.first > 0 || crew.present < planned ? 1 : 0);
+    return crew.present != (int)(uint32_t)kRunEnded;
+}
+
+// At launch index k of 0 .. last, ahead of its work and with all of r_k read,
+// while workgroups are missing: at even indices, how many share the work from
+// here on; at odd ones the first workgroup announces that for the next, and the
+// announcement arrives before its positions do.  (None for the last index, whose
+// positions nobody waits for.)
+__device__ __forceinline__ void share_work(uint32_t* reg, Crew& crew, int planned, int k, int last)
+{
+    if (crew.present >= planned && k != crew.first) return;
+    // (every wave reads the same word: the next is written after this index)
+    if (k > 0 && (k & 1) == 0 && k < last)
+        crew.present = __builtin_amdgcn_readfirstlane((int)(uint32_t)load_word(crew_word(reg)));
+    // state that others stored is read from here on
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    if (crew.rank == 0 && (k & 1) == 1 && k + 1 < last && threadIdx.x == 0) {
+        const uint64_t count =
+            __hip_atomic_load(&reg[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(crew_word(reg), (uint64_t)(k + 1) << 32 | count, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+}
+
+// After the last index: those that were never counted in need not wait longer.
+__device__ __forceinline__ void end_run(uint32_t* reg, const Crew& crew, int planned)
+{
+    if (crew.rank == 0 && crew.present < planned && threadIdx.x == 0)
+        __hip_atomic_store(crew_word(reg), kRunEnded, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // x + y with x rounded first (no fused multiply-add).
@@ -167,44 +233,55 @@ struct Word {
     double* slot;   // in exchange buffer 0; buffers are `words` apart
 };
 
-// Ahead of the sweep at launch index i (cur = (i - i0) mod 3): the word of
-// r_{i-1} is reset; returns the velocity.
+// Where a launch index k of 0 .. last (the run's index i0 + k) stands: which thirds
+// of the exchange hold r_k, r_{k-1} and r_{k+1}, and whether the step from r_{k-1}
+// closes there and the one to r_{k+1} opens.  (32 bits and launch-relative: the
+// scalar unit compares no signed 64-bit numbers.)
+struct Index {
+    int k, last, cur;   // cur: k mod 3
+    bool closes, opens;
+    __device__ __forceinline__ int before() const { return cur == 0 ? 2 : cur - 1; }
+    __device__ __forceinline__ int after() const { return cur == 2 ? 0 : cur + 1; }
+};
+
+// Ahead of the sweep at index x: the word of r_{k-1} is reset; returns the
+// velocity.
 __device__ __forceinline__ double word_begin(const GroupArgs& A, const Word& w, int words,
-                                             int64_t i, int cur)
+                                             const Index& x)
 {
     if (!w.mine) return 0.0;
-    if (i > A.i0 + 1 && i < A.i1)
-        __hip_atomic_store(w.slot + (cur == 0 ? 2 : cur - 1) * words,
-                           __builtin_bit_cast(double, kSentinel), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-    return A.steps > 0 && w.comp < 3 ? A.vel[w.e] : 0.0;
+    if (x.k > 1 && x.k < x.last)
+        __hip_atomic_store(w.slot + x.before() * words, __builtin_bit_cast(double, kSentinel),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return (x.closes || x.opens) && w.comp < 3 ? A.vel[w.e] : 0.0;
 }
 
-// With the acceleration a: kicks and drift, r_{i+1} published.  r0: the word at
-// r_i.  Returns whether all of it is finite.
+// With the acceleration a: kicks and drift, r_{k+1} published.  r0: the word at
+// r_k.  Returns whether all of it is finite.
 __device__ __forceinline__ bool word_finish(const GroupArgs& A, const Word& w, int words,
-                                            int64_t i, int cur, double a, double v, double r0,
-                                            double hdt)
+                                            const Index& x, double a, double v, double r0,
+                                            double hdt, bool moving)
 {
     double r = r0;
     if (w.comp < 3) {
         // (rounded as the step epilogue rounds it)
-        if (i > 0) v = __builtin_fma(hdt, a, v);
-        if (i < A.steps) {
+        if (x.closes) v = __builtin_fma(hdt, a, v);
+        if (x.opens) {
             v = add_rounded(hdt * a, v);
             r = __builtin_fma(A.dt, v, r0);
         }
     }
-    if (i < A.i1) {
-        // the reset above has arrived before this word does
+    if (x.k < x.last) {
+        if (moving && w.comp < 3) agent_store(A.vel + w.e, v);
+        // the reset above (and the velocity) has arrived before this word does
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        publish(w.slot + (cur == 2 ? 0 : cur + 1) * words, r);
+        publish(w.slot + x.after() * words, r);
     }
     if (w.comp == 3) return true;
     if (A.acc) A.acc[A.acc_perm ? w.e - w.ep + A.acc_perm[w.ep] : w.e] = a;
-    if (A.traj) A.traj[(i - A.i0) * 3 * A.n + w.e] = r;
-    if (i == A.i1 && A.pos_out) A.pos_out[w.e] = r;
-    if (A.steps > 0) A.vel[w.e] = v;
+    if (A.traj) A.traj[x.k * (3 * A.n) + w.e] = r;
+    if (x.k == x.last && A.pos_out) A.pos_out[w.e] = r;
+    if ((x.closes || x.opens) && !(moving && x.k < x.last)) A.vel[w.e] = v;
     return __builtin_isfinite(a) && __builtin_isfinite(r) && __builtin_isfinite(v);
 }
 
@@ -360,12 +437,11 @@ __global__ __launch_bounds__(NT) void k_group(GroupArgs A)
     }
     const int n = (int)n64;
     const int groups = (n + Tw - 1) / Tw;
-    int rank = 0, present = 1;
+    uint32_t* reg = A.reg + kGroupRegWords * sys;
+    Crew crew = {0, planned, 0, 0};
     if (A.i1 == A.i0) {   // one launch index: no exchange, nobody waits
-        rank = A.units ? A.units[blockIdx.x].rank : (int)blockIdx.x / A.spread;
-        present = planned;
-    } else if (planned > 1 &&
-               !register_workgroup(A.reg + 2 * sys, planned, rank, present)) {
+        crew.rank = A.units ? A.units[blockIdx.x].rank : (int)blockIdx.x / A.spread;
+    } else if (planned > 1 && !register_workgroup(reg, planned, crew)) {
         return;
     }
 
@@ -374,7 +450,8 @@ __global__ __launch_bounds__(NT) void k_group(GroupArgs A)
     const int64_t stride = A.stride;
     const double* pos_in = A.pos_in + body0;
     const int nm = SPLIT ? (int)A.nmaj[sys] : n;
-    for (int q = tid; q < n; q += NT) {
+    // (a workgroup that joins later reads all four words in the exchange)
+    for (int q = crew.first > 0 ? n : tid; q < n; q += NT) {
         const double g = A.G * A.mass[body0 + q];
         body[q] = double4{pos_in[q], pos_in[stride + q], pos_in[2 * stride + q],
                           q < nm ? g
@@ -400,8 +477,8 @@ __global__ __launch_bounds__(NT) void k_group(GroupArgs A)
     int budget = kPollBudget;
     bool bad = false;
 
-    // One virtual group's part of launch index i; cur = (i - i0) mod 3.
-    auto step_group = [&](int vg, int64_t i, int cur) {
+    // One virtual group's part of launch index x.
+    auto step_group = [&](int vg, const Index& x) {
         const int base = vg * Tw;
         Word w;
         w.ep = base + etgt;
@@ -409,7 +486,7 @@ __global__ __launch_bounds__(NT) void k_group(GroupArgs A)
         w.mine = finisher && w.ep < n;
         w.e = body0 + ecomp * stride + w.ep;
         w.slot = xb + 4 * base + el;
-        const double v = word_begin(A, w, xwords, i, cur);
+        const double v = word_begin(A, w, xwords, x);
         double tx[T], ty[T], tz[T], ax[T], ay[T], az[T];
 #pragma unroll
         for (int t = 0; t < T; ++t) {
@@ -470,10 +547,10 @@ __global__ __launch_bounds__(NT) void k_group(GroupArgs A)
             const double sy = row_sum<TT>(ay[t]);
             const double sz = row_sum<TT>(az[t]);
             if (col < TT) {
-                const int x = t0 + t * TT;
-                red[x * D::RS + row] = sx;
-                red[(Tw + x) * D::RS + row] = sy;
-                red[(2 * Tw + x) * D::RS + row] = sz;
+                const int q = t0 + t * TT;
+                red[q * D::RS + row] = sx;
+                red[(Tw + q) * D::RS + row] = sy;
+                red[(2 * Tw + q) * D::RS + row] = sz;
             }
         }
         __syncthreads();
@@ -489,28 +566,36 @@ __global__ __launch_bounds__(NT) void k_group(GroupArgs A)
             if (D::LPE >= 4) a += row_ror<14>(a);   // lane l: l + 2 of its row
             if (D::LPE >= 2) a += row_ror<15>(a);   // lane l: l + 1
             if (w.mine)
-                bad = !word_finish(A, w, xwords, i, cur, a, v, lds[4 * w.ep + ecomp], hdt) || bad;
+                bad = !word_finish(A, w, xwords, x, a, v, lds[4 * w.ep + ecomp], hdt,
+                                   crew.moving) || bad;
         }
     };
 
-    int cur = 0;   // (i - i0) mod 3
-    for (int64_t i = A.i0; i <= A.i1; ++i) {
-        if (i > A.i0) {
+    const int last = (int)(A.i1 - A.i0);
+    const int64_t left = A.steps - A.i0;   // steps still to open
+    const int open_end = left > last ? last + 1 : (int)left;
+    const bool begun = A.i0 > 0;
+    int cur = crew.first % 3;
+    for (int k = crew.first; k <= last; ++k) {
+        if (k > 0) {
             const double* src = xb + cur * xwords;
             for (int x0 = tid; x0 < 2 * n; x0 += D::kB * NT)
                 gather_words<D::kB, NT>(src, x0, 2 * n, reinterpret_cast<double2*>(body), budget);
             __syncthreads();
         }
-        if (groups <= present) {
-            if (rank < groups) step_group(rank, i, cur);
+        if (crew.moving) share_work(reg, crew, planned, k, last);
+        const Index x = {k, last, cur, begun || k > 0, k < open_end};
+        if (groups <= crew.present) {
+            if (crew.rank < groups) step_group(crew.rank, x);
         } else {
-            for (int vg = rank; vg < groups; vg += present) {
-                step_group(vg, i, cur);
+            for (int vg = crew.rank; vg < groups; vg += crew.present) {
+                step_group(vg, x);
                 __syncthreads();   // red is written again
             }
         }
-        cur = cur == 2 ? 0 : cur + 1;
+        cur = x.after();
     }
+    if (crew.moving) end_run(reg, crew, planned);
     if (bad && A.flags) atomicOr(A.flags, 1u);
 }
 
@@ -539,13 +624,13 @@ __global__ __launch_bounds__(NT, MW) void k_group_vjp(GroupVjpArgs A)
     const int n = (int)A.n;
     const int planned = (int)gridDim.x / A.spread;
     const int groups = (n + Tw - 1) / Tw;
-    int rank = 0, present = 1;
-    if (planned > 1 && !register_workgroup(A.reg, planned, rank, present)) return;
+    Crew crew = {0, planned, 0, 0};
+    if (planned > 1 && !register_workgroup(A.reg, planned, crew)) return;
 
     double* held = reinterpret_cast<double*>(body + n);
     double* red = held + (HELD ? 3 * n : 0);
     const double* lds = reinterpret_cast<const double*>(body);
-    for (int q = tid; q < n; q += NT)
+    for (int q = crew.first > 0 ? n : tid; q < n; q += NT)
         body[q] = double4{A.lam_v[q], A.lam_v[n + q], A.lam_v[2 * n + q], A.mass[q]};
     __syncthreads();
 
@@ -559,19 +644,20 @@ __global__ __launch_bounds__(NT, MW) void k_group_vjp(GroupVjpArgs A)
     const int ecomp = el & 3;
     const bool finisher = tid < D::E * D::LPE && tid % D::LPE == 0;
     int budget = kPollBudget;
-    int cur = 0;   // i mod 3
-    for (int64_t i = 0; i < A.count; ++i) {
+    const int last = (int)A.count - 1;
+    int cur = crew.first % 3;   // i mod 3
+    for (int i = crew.first; i <= last; ++i) {
         const bool closing = A.last && i == 0;
         const int64_t k = A.k1 - (i - (A.last ? 1 : 0));   // slot of the position
         const bool start = !closing && A.first && k == 0;
         const double* rp = closing ? A.last : A.seg + k * 3 * A.n;
-        for (int vg = rank; vg < groups; vg += present) {
+        for (int vg = crew.rank; vg < groups; vg += crew.present) {
             const int base = vg * Tw;
             const int ep = base + etgt;
             const bool mine = finisher && ep < n;
             double* slot = A.xbuf + 4 * base + el;
             double* acc = ecomp < 3 ? A.lam_r + (int64_t)ecomp * n + ep : A.g_m + ep;
-            const double old = mine ? *acc : 0.0;
+            double old = mine ? *acc : 0.0;
             // positions: held in LDS, or the first rounds' in registers.  The
             // order is that of each_source: the bodies after the group's own targets,
             // wrapping, then the targets.
@@ -595,16 +681,20 @@ __global__ __launch_bounds__(NT, MW) void k_group_vjp(GroupVjpArgs A)
             };
             if (!HELD)
                 fetch(0);
-            else if (vg == rank)
+            else if (vg == crew.rank)
                 for (int q = tid; q < 3 * n; q += NT) held[q] = rp[q];
-            if (vg == rank && i > 0) {
+            if (vg == crew.rank && i > 0) {
                 const double* src = A.xbuf + cur * xwords;
                 for (int x0 = tid; x0 < 2 * n; x0 += D::kB * NT)
                     gather_words<D::kB, NT>(src, x0, 2 * n, reinterpret_cast<double2*>(body),
                                             budget);
             }
-            if (vg == rank) __syncthreads();
-            if (mine && i > 1 && i + 1 < A.count)
+            if (vg == crew.rank) __syncthreads();
+            if (crew.moving) {
+                if (vg == crew.rank) share_work(A.reg, crew, planned, i, last);
+                if (mine) old = *acc;   // (its owner may have changed)
+            }
+            if (mine && i > 1 && i < last)
                 __hip_atomic_store(slot + (cur == 0 ? 2 : cur - 1) * xwords,
                                    __builtin_bit_cast(double, kSentinel), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
@@ -690,9 +780,10 @@ __global__ __launch_bounds__(NT, MW) void k_group_vjp(GroupVjpArgs A)
                     const double gc = A.G * (closing || start ? 0.5 * A.dt : A.dt);
                     const double r = old + (ecomp < 3 ? gc : -gc) * a;
                     double w = lds[4 * ep + ecomp];
-                    *acc = r;
+                    if (crew.moving) agent_store(acc, r);
+                    else             *acc = r;
                     if (ecomp < 3 && !start) w = __builtin_fma(A.dt, r, w);
-                    if (i + 1 < A.count) {
+                    if (i < last) {
                         // the reset above has arrived before this word does
                         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                         publish(slot + (cur == 2 ? 0 : cur + 1) * xwords, w);
@@ -701,10 +792,11 @@ __global__ __launch_bounds__(NT, MW) void k_group_vjp(GroupVjpArgs A)
                     }
                 }
             }
-            if (groups > present) __syncthreads();   // red is written again
+            if (groups > crew.present) __syncthreads();   // red is written again
         }
         cur = cur == 2 ? 0 : cur + 1;
     }
+    if (crew.moving) end_run(A.reg, crew, planned);
 }
 
 __global__ __launch_bounds__(256) void k_group_init(double* __restrict__ xbuf, int64_t words,
@@ -747,16 +839,17 @@ hipError_t launch_vjp_shape(const GroupVjpArgs& A, int blocks, size_t lds, hipSt
     const hipError_t e =
         allow_lds(reinterpret_cast<const void*>(&k_group_vjp<T, TT, NT, HELD, MW>), allowed);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_group_vjp<T, TT, NT, HELD, MW>), dim3((unsigned)(blocks * A.spread)), dim3(NT), lds,
-                       s, A);
+    hipLaunchKernelGGL((k_group_vjp<T, TT, NT, HELD, MW>), dim3((unsigned)(blocks * A.spread)),
+                       dim3(NT), lds, s, A);
     return hipGetLastError();
 }
 
 hipError_t init_exchange(double* xbuf, int64_t words, uint32_t* reg, int nsys, hipStream_t s)
 {
-    const int64_t m = words > 2 * nsys ? words : 2 * nsys;
+    const int nreg = kGroupRegWords * nsys;
+    const int64_t m = words > nreg ? words : nreg;
     hipLaunchKernelGGL(k_group_init, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, xbuf,
-                       words, reg, 2 * nsys);
+                       words, reg, nreg);
     return hipGetLastError();
 }
 

@@ -1,7 +1,7 @@
 """Builds the GPU test instruments of tests/host (gfx950): libclockprobe.so
-from clock_probe.hip and libtimelineprobe.so from timeline_probe.hip.  Called
-by the repository's build() beside the library's own build; nothing here is
-part of the library."""
+from clock_probe.hip, libtimelineprobe.so from timeline_probe.hip and
+libgroupprobe.so from group_probe.hip.  Called by the repository's build()
+beside the library's own build; nothing here is part of the library."""
 from __future__ import annotations
 
 import os
@@ -12,6 +12,7 @@ ROOT = os.path.dirname(os.path.dirname(HERE))
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 CLOCK_PROBE = os.path.join(HERE, "libclockprobe.so")
 TIMELINE_PROBE = os.path.join(HERE, "libtimelineprobe.so")
+GROUP_PROBE = os.path.join(HERE, "libgroupprobe.so")
 
 
 def _build_one(src: str, out: str, verbose: bool) -> str:
@@ -32,6 +33,7 @@ def _build_one(src: str, out: str, verbose: bool) -> str:
 
 def build(verbose: bool = False) -> str:
     _build_one("timeline_probe.hip", TIMELINE_PROBE, verbose)
+    _build_one("group_probe.hip", GROUP_PROBE, verbose)
     return _build_one("clock_probe.hip", CLOCK_PROBE, verbose)
 
 
