@@ -1757,7 +1757,11 @@ bool batch_group_route(int prec, const int64_t* offs, int32_t ns, GroupShape* sh
 // The group kernel's work list: the workgroups that fit on the chip at once
 // (`slots`) are dealt to the systems so that the longest share is as short as
 // it can be; a system's workgroups go to one XCD (workgroups go to the XCDs in
-// turn), whose L2 then carries its exchange.
+// turn), whose L2 then carries its exchange.  Only workgroups of the same system
+// wait for each other: systems of one workgroup take turns in a slot, so many
+// small ones leave the others theirs (us per step, one system of 2,000 bodies and
+// 2,000 of 5: 12, by launches 108; 1,012 where each of the small ones had a slot
+// and the large one a single workgroup).
 std::shared_ptr<BatchPlan> batch_group_plan(const int64_t* offs, int32_t ns, const GroupShape& g,
                                             int slots)
 {
@@ -1773,24 +1777,32 @@ std::shared_ptr<BatchPlan> batch_group_plan(const int64_t* offs, int32_t ns, con
     std::vector<int32_t> wgs(ns), order(ns);
     auto size = [&](int32_t k) { return offs[k + 1] - offs[k]; };
     // a workgroup that takes r virtual groups of a system of n bodies needs about
-    // r (n + 64): the workgroups needed when no share takes longer than `time`
+    // r (n + 64), a step's latency about kTurn of these: the slots needed when no
+    // share, and no slot's turns together, take longer than `time`
+    constexpr double kTurn = 512.0;
     auto needed = [&](double time) {
-        int64_t sum = 0;
+        double sum = 0.0;
         for (int32_t k = 0; k < ns; ++k) {
             const int64_t groups = (size(k) + tw - 1) / tw;
-            const double r = std::floor(time / (double)(size(k) + 64));
+            const double cost = (double)(size(k) + 64);
+            const double r = std::floor(time / cost);
             const int64_t share = std::max<int64_t>(1, r < (double)groups ? (int64_t)r : groups);
             wgs[k] = (int32_t)((groups + share - 1) / share);
-            sum += wgs[k];
+            const double turn = std::max(cost * (double)groups, kTurn);
+            sum += wgs[k] > 1 ? (double)wgs[k] : std::min(1.0, turn / std::max(time, 1.0));
         }
         return sum;
     };
     double lo = 0.0, hi = 0.0;   // hi: every system has one workgroup
+    double turns = 0.0;
     for (int32_t k = 0; k < ns; ++k) {
         bp->n_max = std::max(bp->n_max, size(k));
-        hi = std::max(hi, (double)(size(k) + 64) * (double)((size(k) + tw - 1) / tw));
+        const double cost = (double)(size(k) + 64) * (double)((size(k) + tw - 1) / tw);
+        hi = std::max(hi, cost);
+        turns += std::max(cost, kTurn);
         order[k] = k;
     }
+    hi = std::max(hi, turns / slots);
     for (int step = 0; step < 60 && hi - lo > 1.0; ++step) {
         const double mid = 0.5 * (lo + hi);
         (needed(mid) <= slots ? hi : lo) = mid;
