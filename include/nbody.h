@@ -302,8 +302,9 @@ typedef struct {
     int32_t variant;
 } nbody_tile;
 
-/* The tile shape the library will use for (kind, precision, n): the tuned
- * one if nbody_autotune ran for that size class, else a heuristic.
+/* The tile shape the library will use for (kind, precision, n) where it uses
+ * one (work that stays on the chip, above, has none): the tuned one if
+ * nbody_autotune ran for that size class, else a heuristic.
  * kind: 0 = force pass, 1 = adjoint pass, 2 = batched ensemble (n is
  * ignored; chunks are chosen per system; without a tuned tile this reports
  * the one-way heuristic, while a run may take variant 5 from its system
@@ -313,6 +314,13 @@ int32_t nbody_get_tile(int32_t kind, int32_t precision, int64_t n, nbody_tile* t
 /* Force a tile shape for (kind, precision, n's size class); shapes outside
  * the supported set return NBODY_EINVAL. */
 int32_t nbody_set_tile(int32_t kind, int32_t precision, int64_t n, const nbody_tile* tile_host);
+
+/* Installs a tile that nbody_autotune or nbody_autotune_batched chose earlier
+ * (in another process, say), with the effect that their own choice had: work
+ * that stays on the chip (above) goes on doing so, which is faster than any
+ * tile there.  Arguments and errors as for nbody_set_tile. */
+int32_t nbody_set_tuned_tile(int32_t kind, int32_t precision, int64_t n,
+                             const nbody_tile* tile_host);
 
 /* Time candidate tile shapes for (kind, precision) on the caller's data with
  * HIP events and keep the fastest for n's size class.  pos and mass as for
@@ -337,7 +345,8 @@ int32_t nbody_autotune_batched(int32_t precision, const double* pos, const doubl
  * kind 1: the adjoint's transpose-Jacobian pass) over `reps` back-to-back
  * launches with the current tile shape, timed by HIP events recorded on
  * `stream` around the force kernels only.  Inputs as for nbody_accel (kind 1
- * uses a constant cotangent).  Synchronises `stream`. */
+ * uses a constant cotangent).  (Not the kernels that stay on the chip: the
+ * time of a tile can be had at any size.)  Synchronises `stream`. */
 int32_t nbody_time_force(int32_t kind, int32_t precision, const double* pos, const double* mass,
                          int64_t n, double G, double small_mass, int32_t reps,
                          void* workspace, size_t workspace_bytes, void* stream,

@@ -28,8 +28,8 @@ EXPORTS = (
     "nbody_rk4_run",
     "nbody_verlet_adjoint", "nbody_verlet_checkpoints", "nbody_verlet_adjoint_from_checkpoints",
     "nbody_verlet_run_batched", "nbody_energy", "nbody_momenta", "nbody_get_flags",
-    "nbody_get_tile", "nbody_set_tile", "nbody_autotune", "nbody_autotune_batched",
-    "nbody_time_force", "nbody_reset_caches",
+    "nbody_get_tile", "nbody_set_tile", "nbody_set_tuned_tile",
+    "nbody_autotune", "nbody_autotune_batched", "nbody_time_force", "nbody_reset_caches",
     "nbody_last_error", "nbody_version",
 )
 
@@ -102,6 +102,8 @@ def load():
         lib.nbody_get_tile.argtypes = [_I32, _I32, _I64, ctypes.POINTER(Tile)]
         lib.nbody_set_tile.restype = _I32
         lib.nbody_set_tile.argtypes = [_I32, _I32, _I64, ctypes.POINTER(Tile)]
+        lib.nbody_set_tuned_tile.restype = _I32
+        lib.nbody_set_tuned_tile.argtypes = [_I32, _I32, _I64, ctypes.POINTER(Tile)]
         lib.nbody_autotune.restype = _I32
         lib.nbody_autotune.argtypes = [_I32, _I32, _P, _P, _I64, _D, _D, _P, _SZ, _P,
                                        ctypes.POINTER(Tile), ctypes.POINTER(_D)]

@@ -60,7 +60,8 @@ constexpr int64_t kMaxBodies = (int64_t)1 << 30;
 std::mutex g_mu;
 struct TunedTile {
     Tile tile;
-    bool forced;   // nbody_set_tile (runs then take this tile at any size)
+    bool forced;   // nbody_set_tile (runs then take this tile at any size); the
+                   // autotuner's tiles leave runs that stay on the chip there
 };
 std::map<std::tuple<int, int, int>, TunedTile> g_tiles;   // (kind, precision, size class)
 
@@ -198,7 +199,12 @@ Tile pick_tile(int kind, int prec, int64_t n)
 // nbody_set_tile chose a tile for the size (us per step, FP64, 300-step runs:
 // 1.55 against 1.43 with one workgroup alone at 64 bodies, 1.76 against 2.44 at
 // 100; 16.0 against 20.8 each pair once at 4,095: above, 256 workgroups of 16
-// targets would not hold the system, nor LDS its sources).
+// targets would not hold the system, nor LDS its sources).  The autotuner's tiles
+// do not change that: none is faster (us per step, 400-step runs, against the best
+// of its tiles, FP64 and split: 1.72 and 1.63 against 1.83 and 2.12 at 80 bodies,
+// 1.9 and 1.9 against 4.0 and 4.1 at 131, 3.5 and 3.7 against 10.1 and 10.7 at
+// 1,000, 13.7 and 12.0 against 15.1 and 15.4 at 3,500, 15.8 and 13.7 against 17.9
+// and 16.3 at 4,095).
 constexpr int64_t kGroupMin = 80;
 constexpr int64_t kGroupMax = 4095;
 
@@ -1164,9 +1170,11 @@ int32_t nbody_get_tile(int32_t kind, int32_t precision, int64_t n, nbody_tile* t
     return NBODY_OK;
 }
 
-int32_t nbody_set_tile(int32_t kind, int32_t precision, int64_t n, const nbody_tile* tile_host)
+// Checks a tile and enters it: as the caller's choice for runs too (forced), or
+// as the autotuner's.
+static int store_tile(int32_t kind, int32_t precision, int64_t n, const nbody_tile* tile_host,
+                      bool forced)
 {
-    g_err.clear();
     if (!tile_host || kind < 0 || kind > 2 || (kind != 2 && n < 1))
         return fail(NBODY_EINVAL, "bad arguments");
     NB_TRY(check_prec(precision, 0.0));
@@ -1180,8 +1188,21 @@ int32_t nbody_set_tile(int32_t kind, int32_t precision, int64_t n, const nbody_t
         return fail(NBODY_EINVAL, "unsupported tile (%d, %d, %d, variant %d) for kind %d",
                     t.tpl, t.waves, t.chunks, t.variant, kind);
     std::lock_guard<std::mutex> lk(g_mu);
-    g_tiles[std::make_tuple(kind, precision, size_class(n))] = TunedTile{t, true};
+    g_tiles[std::make_tuple(kind, precision, size_class(n))] = TunedTile{t, forced};
     return NBODY_OK;
+}
+
+int32_t nbody_set_tile(int32_t kind, int32_t precision, int64_t n, const nbody_tile* tile_host)
+{
+    g_err.clear();
+    return store_tile(kind, precision, n, tile_host, true);
+}
+
+int32_t nbody_set_tuned_tile(int32_t kind, int32_t precision, int64_t n,
+                             const nbody_tile* tile_host)
+{
+    g_err.clear();
+    return store_tile(kind, precision, n, tile_host, false);
 }
 
 void nbody_reset_caches(void)

@@ -325,9 +325,10 @@ def save_tuning(path):
 
 
 def load_tuning(path, strict_device=True):
-    """Installs tile shapes from a save_tuning() file; returns how many.
-    With strict_device, a file written on another device or library version
-    is ignored (returns 0)."""
+    """Installs tile shapes from a save_tuning() file, with the effect that
+    the autotuner's own choice had; returns how many.  With strict_device, a
+    file written on another device or library version is ignored (returns
+    0)."""
     with open(path) as fh:
         doc = json.load(fh)
     if strict_device and (doc.get("device") != torch.cuda.get_device_name()
@@ -336,8 +337,10 @@ def load_tuning(path, strict_device=True):
     count = 0
     for e in doc.get("entries", []):
         t = e["tile"]
-        set_tile(e["kind"], e["precision"], e["n"], t["targets_per_lane"], t["waves"],
-                 t["chunks"], t["variant"])
+        tile = C.Tile(int(t["targets_per_lane"]), int(t["waves"]), int(t["chunks"]),
+                      int(t["variant"]))
+        C.check(C.load().nbody_set_tuned_tile(int(e["kind"]), _prec(e["precision"]), int(e["n"]),
+                                              ctypes.byref(tile)), "nbody_set_tuned_tile")
         _tuned[(e["kind"], e["precision"], e["n"])] = t
         count += 1
     return count
