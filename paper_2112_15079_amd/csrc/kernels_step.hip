@@ -161,8 +161,8 @@ __global__ __launch_bounds__(kBlock) void k_scatter(const int32_t* __restrict__ 
     else       b[(int64_t)(k - 3) * n + perm[i]] = b_c[(int64_t)(k - 3) * n + i];
 }
 
-// Class order (split form), one launch: workgroup (x, y) places slice x of
-// system y.  It counts the system's heavy bodies itself, before its slice
+// Class order (split form), one launch: workgroup (x, y) places slice y of
+// system x.  It counts the system's heavy bodies itself, before its slice
 // and in all, instead of waiting for the other slices' counts (8 n bytes read
 // from L2 per workgroup: 2 us at 10,425 bodies, where one workgroup that scans
 // slice after slice took 23 us and three gathers and a scale followed it);
@@ -188,10 +188,10 @@ __global__ __launch_bounds__(kPart) void k_class_order(ClassOrder P)
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int w = tid >> 6;
-    const int64_t b0 = P.offsets ? P.offsets[blockIdx.y] : 0;
-    const int64_t b1 = P.offsets ? P.offsets[blockIdx.y + 1] : P.n;
-    const int64_t per = ((b1 - b0 + gridDim.x - 1) / gridDim.x + kPart - 1) / kPart * kPart;
-    const int64_t s0 = b0 + blockIdx.x * per;
+    const int64_t b0 = P.offsets ? P.offsets[blockIdx.x] : 0;
+    const int64_t b1 = P.offsets ? P.offsets[blockIdx.x + 1] : P.n;
+    const int64_t per = ((b1 - b0 + gridDim.y - 1) / gridDim.y + kPart - 1) / kPart * kPart;
+    const int64_t s0 = b0 + blockIdx.y * per;
     const int64_t s1 = s0 + per < b1 ? s0 + per : b1;
     if (s0 >= b1) return;
 
@@ -216,7 +216,7 @@ __global__ __launch_bounds__(kPart) void k_class_order(ClassOrder P)
         major += s_before[k];
         total += s_all[k];
     }
-    if (blockIdx.x == 0 && tid == 0) P.nmaj[blockIdx.y] = total;
+    if (blockIdx.y == 0 && tid == 0) P.nmaj[blockIdx.x] = total;
     int64_t small = total + (s0 - b0) - major;   // next place of each class
 
     int buf = 0;
@@ -497,9 +497,12 @@ hipError_t launch_class_order(const double* pos, const double* vel, const double
                               double* pos_c, double* vel_c, double* mass_c, double* gm_c,
                               hipStream_t s)
 {
-    // slices of 1,024 bodies, fewer and longer ones for large systems
+    // slices of 1,024 bodies, fewer and longer ones for large systems and for many
+    // (every system has as many as the largest); the systems along x, which
+    // alone takes more than 65,535
+    const int64_t most = num_systems < 64 ? 1024 : num_systems < 65536 ? 65536 / num_systems : 1;
     const int64_t slices = (n_max + kPart - 1) / kPart;
-    const dim3 grid((unsigned)(slices < 1024 ? slices : 1024), (unsigned)num_systems);
+    const dim3 grid((unsigned)num_systems, (unsigned)(slices < most ? slices : most));
     const ClassOrder P{pos, vel, mass, offsets, n, threshold, G, perm, nmaj,
                        pos_c, vel_c, mass_c, gm_c};
     hipLaunchKernelGGL(k_class_order, grid, dim3(kPart), 0, s, P);
