@@ -346,21 +346,20 @@ __global__ __launch_bounds__(kRowTile) void k_energy_tiles(const double* __restr
         for (int64_t j0 = c0 > row0 ? c0 : row0; j0 < c1; j0 += kSrcTile) {
             __syncthreads();
             const int64_t j = j0 + tid;
-            if (tid < kSrcTile)   // (past the end: massless and far away)
-                src[tid] = j < c1 ? double4{pos[j], pos[n + j], pos[2 * n + j], mass[j]}
-                                  : double4{1.0e18, 1.0e18, 1.0e18, 0.0};
+            const int cnt = c1 - j0 < kSrcTile ? (int)(c1 - j0) : kSrcTile;
+            if (tid < cnt) src[tid] = double4{pos[j], pos[n + j], pos[2 * n + j], mass[j]};
             __syncthreads();
             auto term = [&](const double4& b) {
                 const double dx = b.x - px, dy = b.y - py, dz = b.z - pz;
                 const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
                 return b.w * rinv_f64(r2);
             };
-            if (j0 >= row0 + kRowTile) {   // every source is past every row
+            if (j0 >= row0 + kRowTile && cnt == kSrcTile) {   // all past every row
 #pragma unroll 4
                 for (int k = 0; k < kSrcTile; ++k) cadd7(acc, term(src[k]));
             } else {
 #pragma unroll 4
-                for (int k = 0; k < kSrcTile; ++k) {
+                for (int k = 0; k < cnt; ++k) {
                     const double e = term(src[k]);
                     cadd7(acc, j0 + k > q ? e : 0.0);
                 }
