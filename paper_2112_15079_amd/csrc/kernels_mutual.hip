@@ -954,12 +954,14 @@ __global__ __launch_bounds__(64 * KMW) void k_force_mutual(const double* __restr
 }
 
 // A small FP64 pass, every pair (the diagonal ones too) as four workgroups of
-// the whole pair's wave layout, workgroup h over sub-phase h.  A whole pair's
-// sweep takes 14 us however few there are (one wave per SIMD, each a serial
-// chain of 64 steps), a quarter's 3.5, and three of them fit beside each other on a
-// CU: up to 192 pairs a step takes 18.1 us where it took 20.9 (4,096 and 4,500
-// bodies), 19.7 where it took 21.0 (4,800).  (Four to a CU: 21.7 against 21.1 at
-// 5,000; halves, of which a CU then gets two: 20.8.)
+// the whole pair's wave layout, workgroup h over sub-phase h.  Bound by the balance
+// of FP64 issue over the CUs: a whole pair's sweep takes 14 us, 11.9 of them
+// issue (26,000 quad-cycles over its CU's four SIMDs at 2.2 GHz), and up to 256 pairs
+// sit one to a CU while the other CUs have nothing.  As quarters, at most three
+// to a CU, a pass is three quarters of that: up to 192 pairs a step takes 18.1 us
+// where it took 20.9 (4,096 and 4,500 bodies), 19.7 where it took 21.0 (4,800).
+// (Four to a CU: 21.7 against 21.1 at 5,000; halves, of which a CU then gets
+// two: 20.8.)
 // Workgroups 0 .. 4 R - 1 run the diagonals, the others go along the
 // super-diagonals (wrapped past range R - 1).  A body of range X meets every
 // range Y in each sub-phase, whose sum (or reaction) goes to slot h R + Y.
