@@ -1795,33 +1795,40 @@ std::shared_ptr<BatchPlan> batch_group_plan(const int64_t* offs, int32_t ns, con
     evict_batch_plan_locked();
     auto bp = std::make_shared<BatchPlan>();
     const int64_t tw = (int64_t)g.tpl * g.lanes;
-    std::vector<int32_t> wgs(ns), order(ns);
     auto size = [&](int32_t k) { return offs[k + 1] - offs[k]; };
+    // by size (at most kGroupBatchMax of them, however many systems): systems
+    // and workgroups of each
+    std::vector<int32_t> count(kGroupBatchMax + 1), wgs(kGroupBatchMax + 1);
+    for (int32_t k = 0; k < ns; ++k) {
+        ++count[size(k)];
+        bp->n_max = std::max(bp->n_max, size(k));
+    }
     // a workgroup that takes r virtual groups of a system of n bodies needs about
     // r (n + 64), a step's latency about kTurn of these: the slots needed when no
     // share, and no slot's turns together, take longer than `time`
     constexpr double kTurn = 512.0;
     auto needed = [&](double time) {
         double sum = 0.0;
-        for (int32_t k = 0; k < ns; ++k) {
-            const int64_t groups = (size(k) + tw - 1) / tw;
-            const double cost = (double)(size(k) + 64);
+        for (int64_t n = 1; n <= bp->n_max; ++n) {
+            if (!count[n]) continue;
+            const int64_t groups = (n + tw - 1) / tw;
+            const double cost = (double)(n + 64);
             const double r = std::floor(time / cost);
             const int64_t share = std::max<int64_t>(1, r < (double)groups ? (int64_t)r : groups);
-            wgs[k] = (int32_t)((groups + share - 1) / share);
+            wgs[n] = (int32_t)((groups + share - 1) / share);
             const double turn = std::max(cost * (double)groups, kTurn);
-            sum += wgs[k] > 1 ? (double)wgs[k] : std::min(1.0, turn / std::max(time, 1.0));
+            sum += count[n] * (wgs[n] > 1 ? (double)wgs[n]
+                                          : std::min(1.0, turn / std::max(time, 1.0)));
         }
         return sum;
     };
     double lo = 0.0, hi = 0.0;   // hi: every system has one workgroup
     double turns = 0.0;
-    for (int32_t k = 0; k < ns; ++k) {
-        bp->n_max = std::max(bp->n_max, size(k));
-        const double cost = (double)(size(k) + 64) * (double)((size(k) + tw - 1) / tw);
+    for (int64_t n = 1; n <= bp->n_max; ++n) {
+        if (!count[n]) continue;
+        const double cost = (double)(n + 64) * (double)((n + tw - 1) / tw);
         hi = std::max(hi, cost);
-        turns += std::max(cost, kTurn);
-        order[k] = k;
+        turns += count[n] * std::max(cost, kTurn);
     }
     hi = std::max(hi, turns / slots);
     for (int step = 0; step < 60 && hi - lo > 1.0; ++step) {
@@ -1829,28 +1836,34 @@ std::shared_ptr<BatchPlan> batch_group_plan(const int64_t* offs, int32_t ns, con
         (needed(mid) <= slots ? hi : lo) = mid;
     }
     (void)needed(hi);
-    std::stable_sort(order.begin(), order.end(),
-                     [&](int32_t a, int32_t b) { return size(a) > size(b); });
+    std::vector<int32_t> order(ns), place(kGroupBatchMax + 1);   // largest first, stable
+    for (int64_t n = bp->n_max; n > 0; --n) place[n - 1] = place[n] + count[n];
+    for (int32_t k = 0; k < ns; ++k) order[place[size(k)]++] = k;
     // one list per XCD; a system that no list has room for is spread over all
     constexpr int kXcds = 8;
     std::vector<GroupUnit> lists[kXcds];
+    size_t length[kXcds] = {};
     auto shortest = [&] {
-        return std::min_element(lists, lists + kXcds, [](const auto& a, const auto& b) {
-            return a.size() < b.size();
-        });
+        int m = 0;
+        for (int l = 1; l < kXcds; ++l)
+            if (length[l] < length[m]) m = l;
+        return m;
     };
     for (int32_t k : order) {
-        auto* l = shortest();
-        const bool whole = (int64_t)l->size() + wgs[k] <= slots / kXcds;
-        for (int32_t r = 0; r < wgs[k]; ++r)
-            (whole ? l : shortest())->push_back(
-                GroupUnit{offs[k], (int32_t)size(k), k, wgs[k], r});
+        const int32_t nk = (int32_t)size(k), w = wgs[nk];
+        const int l = shortest();
+        const bool whole = (int64_t)length[l] + w <= slots / kXcds;
+        for (int32_t r = 0; r < w; ++r) {
+            const int m = whole || r == 0 ? l : shortest();
+            lists[m].push_back(GroupUnit{offs[k], nk, k, w, r});
+            ++length[m];
+        }
     }
     // in turn, short lists padded (n = 0); unpadded, and so without regard to
     // XCDs, where the padding would outgrow the workspace's room for units
-    size_t len = 0;
-    for (const auto& l : lists) len = std::max(len, l.size());
+    const size_t len = *std::max_element(length, length + kXcds);
     const bool pad = (int64_t)(kXcds * len) <= offs[ns] / 4 + ns;
+    bp->group_units.reserve(kXcds * len);
     for (size_t i = 0; i < len; ++i)
         for (const auto& l : lists)
             if (i < l.size()) bp->group_units.push_back(l[i]);
