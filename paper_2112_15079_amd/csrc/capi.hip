@@ -1741,10 +1741,12 @@ int batched_split_prepare(const double* pos, const double* vel, const double* ma
 // when the chip is full, and a tail of 50 to 100 us).
 constexpr int64_t kGroupBatchMax = 2048;
 constexpr double kGroupBatchPairs = 3e8;
+// (a launch takes at most 2^32 threads: 16.7 million systems of one workgroup)
+constexpr int32_t kGroupBatchSystems = 1 << 22;
 
 bool batch_group_route(int prec, const int64_t* offs, int32_t ns, GroupShape* shape, int* slots)
 {
-    if (prec == NBODY_SPLIT_COMPENSATED) return false;
+    if (prec == NBODY_SPLIT_COMPENSATED || ns > kGroupBatchSystems) return false;
     {
         std::lock_guard<std::mutex> lk(g_mu);
         auto it = g_tiles.find(std::make_tuple(2, prec, size_class(0)));

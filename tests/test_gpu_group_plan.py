@@ -48,3 +48,19 @@ def test_first_call_on_new_offsets(ns):
             times[route] = min(times[route], call(offs, state))
     nb.reset_caches()
     assert times["here"] <= 1.2 * times["by launches"], times
+
+
+@pytest.mark.parametrize("ns", [1 << 22, (1 << 22) + 1, 17_000_000])
+def test_more_systems_than_a_launch_has_threads_for(ns):
+    """Single bodies drift: a launch of 2^32 threads holds 16.7 million workgroups of
+    256, so many systems go by launches."""
+    nb.reset_caches()
+    offs = np.arange(ns + 1, dtype=np.int64)
+    pos = torch.rand(3, ns, dtype=torch.float64, device=DEV)
+    vel = torch.rand(3, ns, dtype=torch.float64, device=DEV)
+    mass = torch.full((ns,), 1e-9, dtype=torch.float64, device=DEV)
+    # (the drift is a fused multiply-add: half an ulp of the result from this)
+    want = pos + 0.1 * vel + 0.1 * vel
+    call(offs, [pos, vel, mass], steps=2)
+    assert bool((torch.abs(pos - want) <= 2 ** -51 * want).all())
+    nb.reset_caches()
