@@ -224,7 +224,8 @@ int32_t nbody_verlet_adjoint_from_checkpoints(const double* checkpoints, const d
  * of different systems do not interact.  offsets_host is a HOST array of
  * num_systems + 1 non-decreasing values starting at 0; every system has at
  * least one body.  Ensembles of small systems (none above 2,048 bodies, sum
- * n_k^2 at most 3e8, no tile from nbody_set_tile) run in workgroups that stay on the chip;
+ * n_k^2 at most 1e8, or at most 3e8 where that is estimated to be faster, no
+ * tile from nbody_set_tile) run in workgroups that stay on the chip;
  * otherwise the step loop is captured into a HIP graph on first use
  * and replayed.  Tile: the one nbody_autotune_batched chose, else each pair
  * once (variant 5, (4, 4)) when every system has at most 10,240 bodies and

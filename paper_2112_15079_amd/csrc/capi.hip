@@ -1732,15 +1732,108 @@ int batched_split_prepare(const double* pos, const double* vel, const double* ma
     return NBODY_OK;
 }
 
+// Largest system of an ensemble that runs in the group kernel.
+constexpr int64_t kGroupBatchMax = 2048;
+
+// How the workgroups that fit on the chip at once (`slots`) are dealt to the systems
+// of an ensemble: so that the longest share is as short as it can be.  By
+// size, at most kGroupBatchMax of them however many systems: systems and
+// workgroups of each.  A workgroup that takes r virtual groups of tw targets of a
+// system of n bodies needs about r (n + 64); systems of one workgroup take turns
+// in a slot, a step's latency, about kTurn of these units, at least.
+struct GroupShares {
+    int64_t n_max = 0, tw = 0;
+    std::vector<int32_t> count, wgs;
+    double time = 0.0;   // of the longest share, or of a slot's turns together
+
+    int64_t groups(int64_t n) const { return (n + tw - 1) / tw; }
+    static double cost(int64_t n) { return (double)(n + 64); }
+};
+
+GroupShares group_shares(const int64_t* offs, int32_t ns, int64_t tw, int slots)
+{
+    constexpr double kTurn = 512.0;
+    GroupShares S;
+    S.tw = tw;
+    S.count.resize(kGroupBatchMax + 1);
+    S.wgs.resize(kGroupBatchMax + 1);
+    for (int32_t k = 0; k < ns; ++k) {
+        const int64_t n = offs[k + 1] - offs[k];
+        ++S.count[n];
+        S.n_max = std::max(S.n_max, n);
+    }
+    std::vector<int64_t> sizes;
+    for (int64_t n = 1; n <= S.n_max; ++n)
+        if (S.count[n]) sizes.push_back(n);
+    // the slots needed when nothing takes longer than `time`
+    auto needed = [&](double time) {
+        double sum = 0.0;
+        for (int64_t n : sizes) {
+            const int64_t groups = S.groups(n);
+            const double r = std::floor(time / S.cost(n));
+            const int64_t share = std::max<int64_t>(1, r < (double)groups ? (int64_t)r : groups);
+            S.wgs[n] = (int32_t)((groups + share - 1) / share);
+            const double turn = std::max(S.cost(n) * (double)groups, kTurn);
+            sum += S.count[n] * (S.wgs[n] > 1 ? (double)S.wgs[n]
+                                              : std::min(1.0, turn / std::max(time, 1.0)));
+        }
+        return sum;
+    };
+    double lo = 0.0, hi = 0.0;   // hi: every system has one workgroup
+    double turns = 0.0;
+    for (int64_t n : sizes) {
+        const double whole = S.cost(n) * (double)S.groups(n);
+        hi = std::max(hi, whole);
+        turns += S.count[n] * std::max(whole, kTurn);
+    }
+    hi = std::max(hi, turns / slots);
+    for (int step = 0; step < 60 && hi - lo > 1.0; ++step) {
+        const double mid = 0.5 * (lo + hi);
+        (needed(mid) <= slots ? hi : lo) = mid;
+    }
+    (void)needed(hi);
+    S.time = hi;
+    return S;
+}
+
+// Whether a large ensemble is left to the pass by launches, which when the chip is
+// full has the leaner pair loop but ends each pass with a partly filled round:
+// by an estimate of both, us per step, from fits to 720 ensembles of 1e8 to
+// 3e8 pairs in both forms (5 to 95 %: 0.80 to 1.15 and 0.83 to 1.14 of the measured
+// time).  With the factor none of them is more than 3 % slower than by
+// launches (without a choice 58 were, the worst 1.49 times: 280 systems of 998
+// bodies 389 against 261), 430 stay, at 0.47 to 1.03 of the time by launches.
+bool group_shares_lose(const GroupShares& S, double pairs)
+{
+    // by launches: units of 128 targets and at most kBatchChunkLen sources, the longest
+    // first, in turn over the 1,024 SIMDs; the first SIMD's load and rounds
+    int64_t units = 0, first = 0;   // first: unit of the SIMD's next one
+    double load = 0.0;
+    double wgs = 0.0, total = 0.0;
+    for (int64_t n = S.n_max; n > 0; --n) {
+        if (!S.count[n]) continue;
+        const int64_t chunks = (n + kBatchChunkLen - 1) / kBatchChunkLen;
+        units += S.count[n] * chunks * ((n + 127) / 128);
+        for (; first < units; first += 1024) load += (double)((n + chunks - 1) / chunks);
+        wgs += (double)S.count[n] * S.wgs[n];
+        total += (double)S.count[n] * (double)S.groups(n) * S.cost(n);
+    }
+    const double by_launches =
+        23.0 + 0.054 * load + 5.2 * (double)((units + 1023) / 1024) + 0.267e-6 * pairs;
+    const double rounds = wgs / 256.0;   // workgroups per CU
+    const double here =
+        0.0045 * total / 256.0 + 0.0035 * S.time + 11.2 * (std::ceil(rounds) - rounds);
+    return here > 0.8 * by_launches;
+}
+
 // Whether an ensemble runs in the group kernel (and in which shape, with how
 // many workgroups at once): systems of up to kGroupBatchMax bodies too small
-// on average for each pair once, and not so many that the chip is full anyway,
-// where the one-way passes' leaner pair loop wins (us per step against them:
-// 128 systems of 40 to 400 bodies 9.3 / 53, 8 of 300 to 2,000 28 / 109, 120 of
-// 300 to 1,400, 1.1e8 pairs, 102 / 162: 1.07e12 pairs/s against their 1.49e12
-// when the chip is full, and a tail of 50 to 100 us).
-constexpr int64_t kGroupBatchMax = 2048;
+// on average for each pair once, and not so many that the pass by launches is
+// faster (us per step against it: 128 systems of 40 to 400 bodies 9.3 / 53, 8 of
+// 300 to 2,000 28 / 109; of 1,230 ensembles of 1.5e7 to 1e8 pairs none takes more
+// than 1.01 times as long; above, by group_shares_lose, up to 3e8).
 constexpr double kGroupBatchPairs = 3e8;
+constexpr double kGroupBatchAlways = 1e8;
 // (a launch takes at most 2^32 threads: 16.7 million systems of one workgroup)
 constexpr int32_t kGroupBatchSystems = 1 << 22;
 
@@ -1774,17 +1867,16 @@ bool batch_group_route(int prec, const int64_t* offs, int32_t ns, GroupShape* sh
     const size_t lds = group_lds_bytes(n_max, *shape) + 512;
     per_cu = (int)std::min<size_t>(per_cu, ((size_t)160 << 10) / lds);
     *slots = 256 * std::max(per_cu, 1);
-    return true;
+    return pairs <= kGroupBatchAlways ||
+           !group_shares_lose(group_shares(offs, ns, shape->tpl * shape->lanes, *slots), pairs);
 }
 
-// The group kernel's work list: the workgroups that fit on the chip at once
-// (`slots`) are dealt to the systems so that the longest share is as short as
-// it can be; a system's workgroups go to one XCD (workgroups go to the XCDs in
-// turn), whose L2 then carries its exchange.  Only workgroups of the same system
-// wait for each other: systems of one workgroup take turns in a slot, so many
-// small ones leave the others theirs (us per step, one system of 2,000 bodies and
-// 2,000 of 5: 12, by launches 108; 1,012 where each of the small ones had a slot
-// and the large one a single workgroup).
+// The group kernel's work list: a system's workgroups go to one XCD (workgroups
+// go to the XCDs in turn), whose L2 then carries its exchange.  Only workgroups
+// of the same system wait for each other: systems of one workgroup take turns in
+// a slot, so many small ones leave the others theirs (us per step, one system of
+// 2,000 bodies and 2,000 of 5: 12, by launches 108; 1,012 where each of the small
+// ones had a slot and the large one a single workgroup).
 std::shared_ptr<BatchPlan> batch_group_plan(const int64_t* offs, int32_t ns, const GroupShape& g,
                                             int slots)
 {
@@ -1796,50 +1888,11 @@ std::shared_ptr<BatchPlan> batch_group_plan(const int64_t* offs, int32_t ns, con
     if (it != g_batch.end()) return it->second;
     evict_batch_plan_locked();
     auto bp = std::make_shared<BatchPlan>();
-    const int64_t tw = (int64_t)g.tpl * g.lanes;
+    const GroupShares S = group_shares(offs, ns, (int64_t)g.tpl * g.lanes, slots);
+    bp->n_max = S.n_max;
     auto size = [&](int32_t k) { return offs[k + 1] - offs[k]; };
-    // by size (at most kGroupBatchMax of them, however many systems): systems
-    // and workgroups of each
-    std::vector<int32_t> count(kGroupBatchMax + 1), wgs(kGroupBatchMax + 1);
-    for (int32_t k = 0; k < ns; ++k) {
-        ++count[size(k)];
-        bp->n_max = std::max(bp->n_max, size(k));
-    }
-    // a workgroup that takes r virtual groups of a system of n bodies needs about
-    // r (n + 64), a step's latency about kTurn of these: the slots needed when no
-    // share, and no slot's turns together, take longer than `time`
-    constexpr double kTurn = 512.0;
-    auto needed = [&](double time) {
-        double sum = 0.0;
-        for (int64_t n = 1; n <= bp->n_max; ++n) {
-            if (!count[n]) continue;
-            const int64_t groups = (n + tw - 1) / tw;
-            const double cost = (double)(n + 64);
-            const double r = std::floor(time / cost);
-            const int64_t share = std::max<int64_t>(1, r < (double)groups ? (int64_t)r : groups);
-            wgs[n] = (int32_t)((groups + share - 1) / share);
-            const double turn = std::max(cost * (double)groups, kTurn);
-            sum += count[n] * (wgs[n] > 1 ? (double)wgs[n]
-                                          : std::min(1.0, turn / std::max(time, 1.0)));
-        }
-        return sum;
-    };
-    double lo = 0.0, hi = 0.0;   // hi: every system has one workgroup
-    double turns = 0.0;
-    for (int64_t n = 1; n <= bp->n_max; ++n) {
-        if (!count[n]) continue;
-        const double cost = (double)(n + 64) * (double)((n + tw - 1) / tw);
-        hi = std::max(hi, cost);
-        turns += count[n] * std::max(cost, kTurn);
-    }
-    hi = std::max(hi, turns / slots);
-    for (int step = 0; step < 60 && hi - lo > 1.0; ++step) {
-        const double mid = 0.5 * (lo + hi);
-        (needed(mid) <= slots ? hi : lo) = mid;
-    }
-    (void)needed(hi);
     std::vector<int32_t> order(ns), place(kGroupBatchMax + 1);   // largest first, stable
-    for (int64_t n = bp->n_max; n > 0; --n) place[n - 1] = place[n] + count[n];
+    for (int64_t n = bp->n_max; n > 0; --n) place[n - 1] = place[n] + S.count[n];
     for (int32_t k = 0; k < ns; ++k) order[place[size(k)]++] = k;
     // one list per XCD; a system that no list has room for is spread over all
     constexpr int kXcds = 8;
@@ -1852,7 +1905,7 @@ std::shared_ptr<BatchPlan> batch_group_plan(const int64_t* offs, int32_t ns, con
         return m;
     };
     for (int32_t k : order) {
-        const int32_t nk = (int32_t)size(k), w = wgs[nk];
+        const int32_t nk = (int32_t)size(k), w = S.wgs[nk];
         const int l = shortest();
         const bool whole = (int64_t)length[l] + w <= slots / kXcds;
         for (int32_t r = 0; r < w; ++r) {

@@ -50,6 +50,23 @@ def test_first_call_on_new_offsets(ns):
     assert times["here"] <= 1.2 * times["by launches"], times
 
 
+@pytest.mark.parametrize("ns,m", [(280, 998), (300, 899), (282, 862)])
+def test_large_uniform_ensembles(ns, m):
+    """Sizes whose shares fill the chip badly: no slower than by launches."""
+    offs = np.arange(ns + 1, dtype=np.int64) * m
+    state = [torch.rand(3, ns * m, dtype=torch.float64, device=DEV),
+             torch.zeros(3, ns * m, dtype=torch.float64, device=DEV),
+             torch.full((ns * m,), 1e-12, dtype=torch.float64, device=DEV)]
+    nb.reset_caches()
+    times = []
+    for _ in range(2):
+        call(offs, state, 20)
+        times.append(min(call(offs, state, 20) for _ in range(4)))
+        nb.set_tile(2, "fp64", 0, *nb.get_tile(2, "fp64", 0).values())   # (then by launches)
+    nb.reset_caches()
+    assert times[0] <= 1.15 * times[1], times
+
+
 @pytest.mark.parametrize("ns", [1 << 22, (1 << 22) + 1, 17_000_000])
 def test_more_systems_than_a_launch_has_threads_for(ns):
     """Single bodies drift: a launch of 2^32 threads holds 16.7 million workgroups of
