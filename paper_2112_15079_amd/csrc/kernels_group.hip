@@ -35,9 +35,11 @@
 // workgroup that is resident, a run that began on a corner of the chip has all
 // of it soon after other work ends, and results do not depend on how many
 // share the work: a virtual group's arithmetic is the same whoever runs it.
-// (Two runs at once, 1,000 bodies and 1,000 steps each: 7.4 ms, one alone 3.4,
+// (Two runs at once, 1,000 bodies and 1,000 steps each: 7.8 ms, one alone 3.4,
 // and 82 where late workgroups left for the rest of the launch; 4,000 bodies, 500
-// steps: 17, 7.7 and 243.)
+// steps: 17, 7.7 and 243.  Eight at once, us per step of all: 27 at 1,000 bodies,
+// 40 by launches; 42 and 47 at 2,000; 89 and 68 at 3,000, where one workgroup fills
+// a CU's LDS and the runs take turns.)
 //
 // The pair arithmetic and the two forms are those of the multi-kernel passes:
 // FP64, or (SPLIT, class order) heavy sources with one Newton step and light
@@ -59,7 +61,11 @@ constexpr uint64_t kRunEnded = ~(uint64_t)0;
 #define NB_GROUP_REGISTER_TICKS 200000
 #define NB_GROUP_ENTRY(reg)
 #endif
-constexpr uint64_t kRegisterTicks = NB_GROUP_REGISTER_TICKS;   // (2 ms of the 100 MHz counter)
+// How long the first workgroup waits for the others, in ticks of the 100 MHz
+// counter: 0.2 ms, if fewer than a quarter of them have come then 2 ms (a run on
+// a corner of the chip would hold up those that come when it is freed).
+constexpr uint64_t kRegisterTicks = NB_GROUP_REGISTER_TICKS;
+constexpr uint64_t kEnoughTicks = kRegisterTicks / 10;
 constexpr int kPollBudget = 1 << 26;          // polls of a thread, a last resort
 constexpr int kMaxLds = 160 * 1024 - 256;     // beside the kernel's static LDS
 constexpr int kBlkG = 16;                     // FP32 block length of the light sums
@@ -164,9 +170,12 @@ __device__ __forceinline__ bool register_workgroup(uint32_t* reg, int planned, C
         if (r == 0) {   // the first: start the run
             const uint64_t t0 = wall_clock64();
             uint32_t count;
-            while ((count = __hip_atomic_load(&reg[0], __ATOMIC_RELAXED,
-                                              __HIP_MEMORY_SCOPE_AGENT)) < (uint32_t)planned &&
-                   wall_clock64() - t0 < kRegisterTicks) {
+            for (;;) {
+                count = __hip_atomic_load(&reg[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const uint64_t t = wall_clock64() - t0;
+                if (count >= (uint32_t)planned || t >= kRegisterTicks ||
+                    (t >= kEnoughTicks && 4 * count >= (uint32_t)planned))
+                    break;
             }
             word = count;
             reg[1] = count;
@@ -196,11 +205,15 @@ __device__ __forceinline__ bool register_workgroup(uint32_t* reg, int planned, C
 __device__ __forceinline__ void share_work(uint32_t* reg, Crew& crew, int planned, int k, int last)
 {
     if (crew.present >= planned && k != crew.first) return;
-    // (every wave reads the same word: the next is written after this index)
-    if (k > 0 && (k & 1) == 0 && k < last)
-        crew.present = __builtin_amdgcn_readfirstlane((int)(uint32_t)load_word(crew_word(reg)));
-    // state that others stored is read from here on
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    if (k > 0 && (k & 1) == 0 && k < last) {
+        // (every wave reads the same word: the next is written after this index)
+        const int now =
+            __builtin_amdgcn_readfirstlane((int)(uint32_t)load_word(crew_word(reg)));
+        // where work changes hands, state that others stored is read from here on
+        if (now != crew.present || k == crew.first)
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        crew.present = now;
+    }
     if (crew.rank == 0 && (k & 1) == 1 && k + 1 < last && threadIdx.x == 0) {
         const uint64_t count =
             __hip_atomic_load(&reg[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
