@@ -285,7 +285,7 @@ __device__ __forceinline__ bool word_finish(const GroupArgs& A, const Word& w, i
         }
     }
     if (x.k < x.last) {
-        if (moving && w.comp < 3) agent_store(A.vel + w.e, v);
+        if (__builtin_expect(moving, 0) && w.comp < 3) agent_store(A.vel + w.e, v);
         // the reset above (and the velocity) has arrived before this word does
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         publish(w.slot + x.after() * words, r);
@@ -596,7 +596,8 @@ __global__ __launch_bounds__(NT) void k_group(GroupArgs A)
                 gather_words<D::kB, NT>(src, x0, 2 * n, reinterpret_cast<double2*>(body), budget);
             __syncthreads();
         }
-        if (crew.moving) share_work(reg, crew, planned, k, last);
+        // (rare: kept out of the way of the loop)
+        if (__builtin_expect(crew.moving, 0)) share_work(reg, crew, planned, k, last);
         const Index x = {k, last, cur, begun || k > 0, k < open_end};
         if (groups <= crew.present) {
             if (crew.rank < groups) step_group(crew.rank, x);
