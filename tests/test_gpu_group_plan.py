@@ -57,14 +57,16 @@ def test_large_uniform_ensembles(ns, m):
     state = [torch.rand(3, ns * m, dtype=torch.float64, device=DEV),
              torch.zeros(3, ns * m, dtype=torch.float64, device=DEV),
              torch.full((ns * m,), 1e-12, dtype=torch.float64, device=DEV)]
+    times = [1e9, 1e9]
+    for _ in range(4):   # (in turn, so that the clock's rise favours neither)
+        for route in (0, 1):
+            nb.reset_caches()
+            if route:
+                nb.set_tile(2, "fp64", 0, *nb.get_tile(2, "fp64", 0).values())
+            call(offs, state, 20)
+            times[route] = min(times[route], *(call(offs, state, 20) for _ in range(3)))
     nb.reset_caches()
-    times = []
-    for _ in range(2):
-        call(offs, state, 20)
-        times.append(min(call(offs, state, 20) for _ in range(4)))
-        nb.set_tile(2, "fp64", 0, *nb.get_tile(2, "fp64", 0).values())   # (then by launches)
-    nb.reset_caches()
-    assert times[0] <= 1.15 * times[1], times
+    assert times[0] <= 1.15 * times[1], times   # (here, by launches)
 
 
 @pytest.mark.parametrize("ns", [1 << 22, (1 << 22) + 1, 17_000_000])
